@@ -21,6 +21,8 @@
 //           item's visibilities, degrids same-phase neighbours together and
 //           reduces each visibility's taps across the wave; with float32 tables
 //           two workgroups can share an item, one per pair of correlations.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace pg {
@@ -499,187 +501,206 @@ __global__ __launch_bounds__(NW * 64) void grid_banded_kernel(const Item* __rest
 // phase per pass, loading every tap once and applying it to all R rows, whose sub-grid positions
 // differ by wave-uniform offsets.  Waves overlap in the sub-grid, so it is accumulated with LDS
 // integer atomics (on CDNA4 these run at about the rate of plain LDS read-modify-write; float LDS
-// atomics are over an order of magnitude slower), exactly, in two-word fixed point:
+// atomics are over an order of magnitude slower), exactly, in 51-bit fixed point:
 //   * the item's scale 2^e puts B = max_q kbound[plane][q] x rows x the largest row sum
 //     sum_c |Re V_c| + |Im V_c| (a bound on every value of the sub-grid and on the sum of the
-//     magnitudes of its terms, independent of summation order) below 2^29; visibilities are
+//     magnitudes of its terms, independent of summation order) below 2^28; visibilities are
 //     multiplied by 2^e as they are read, so every term y comes out already scaled;
-//   * each term is split into h = floor(y) and l = trunc(fract(y) 2^f), f = min(20, 30 - log2 rows):
-//     coarse words sum to less than 2^30 in magnitude, fine words lie in [0, 2^f) and sum to less
-//     than 2^30, and the pair holds every float32 term to about one fine unit 2^-(e + f), far below
-//     float32 rounding;
-//   * real and imaginary words are packed into one 64-bit integer, im 2^32 + re, whose sums decode
-//     exactly while |sum re| < 2^31: one 64-bit LDS atomic per word pair.  Coarse real words are
-//     sign-extended into the upper half; fine words are never negative, so their pair is the two
-//     32-bit registers side by side.
+//   * y is widened to float64 and added to kFixedMagic = 1.5 2^31, whose unit in the last place is
+//     2^-kFixedBits: the low 51 bits of the sum are y rounded to that unit, as a two's complement
+//     integer, and the constant leaves them zero itself, so adding the bits of the float64 as one
+//     64-bit integer adds the fixed-point value modulo 2^51 (the bits above collect the constant and
+//     are dropped when the word is read).  Sums stay below 2^50 units by the choice of e, so they
+//     are exact, and the unit, B 2^-49, is far below float32 rounding.
 // The sub-grid of an item is therefore the same bits whatever the order of its additions.
+//
+// The real and imaginary words of a value are two such integers in separate halves of the sub-grid
+// ([re | im][q][W][P]), so the 64 lanes of an atomic touch consecutive 8-byte words.
+//
+// What bounds it: per row, tap and plane 34 SIMD cycles of matrix products, 17 of conversion (float64
+// conversions and adds take 4.3) and 5 of addresses, beside two 64-bit LDS atomics (15 cycles of the
+// CU's LDS, shared by four SIMDs) and the tap loads.  On 2.3M rows onto 2048^2 x 4 (float32 tables)
+// the grid takes 2.68 ms against 3.26 ms for the form before it: scalar-operand float FMAs (77
+// cycles), two 32-bit words per value split off by floor and fraction (53), 8 waves.
 constexpr int kSharedScratch = 64;  // bytes after the sub-grid words: the per-wave maxima
+constexpr int kFixedBits = 21;      // fraction bits of a sub-grid word below the scaled unit
+constexpr double kFixedMagic = 3221225472.0;  // 1.5 2^31: one unit in the last place is 2^-21
 
-__device__ __forceinline__ unsigned long long pack_pair(int re, int im) {
-  return static_cast<unsigned long long>((static_cast<long long>(im) << 32) + static_cast<long long>(re));
+__device__ __forceinline__ unsigned long long fixed_bits(float y) {
+  return static_cast<unsigned long long>(__double_as_longlong(static_cast<double>(y) + kFixedMagic));
 }
-__device__ __forceinline__ unsigned long long pack_fine(unsigned re, unsigned im) {
-  return (static_cast<unsigned long long>(im) << 32) | re;
-}
-// floor to int in one instruction (the compiler emits a floor and a truncating conversion)
-__device__ __forceinline__ int floor_to_int(float x) {
-  int r;
-  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
-  return r;
-}
-__device__ __forceinline__ int2 unpack_pair(unsigned long long v) {
-  const int re = static_cast<int>(static_cast<unsigned>(v));
-  const int im = static_cast<int>(static_cast<long long>(v) >> 32) + (re < 0 ? 1 : 0);
-  return make_int2(re, im);
+__device__ __forceinline__ long long fixed_value(unsigned long long word) {
+  return static_cast<long long>(word << 13) >> 13;
 }
 
-// PF: two tap buffers (the next pass's taps in flight); off where the registers would not hold them
-template <int NP, typename TapT, int R, int NQ, bool PF>
-__device__ __forceinline__ void grid_rows_shared(unsigned long long* lds, int fine_off, const TapT* __restrict__ pt,
-                                                 int j, int m_ly, int m_lx, int m_k, const float2* __restrict__ vis,
-                                                 int S, int SS, int P, int WP, float inv_s, const FootStep& step,
-                                                 int lane, int ex, float fscale) {
-  const TapChunks<NQ * NP, TapT> tc(pt, SS);
-  constexpr uint32_t TB = TapChunks<NQ * NP, TapT>::kTapBytes;
-  const int ly0 = __builtin_amdgcn_readlane(m_ly, j), lx0 = __builtin_amdgcn_readlane(m_lx, j);
-  int d[R];
-  float2 v[R][NP];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    d[r] = (__builtin_amdgcn_readlane(m_ly, j + r) - ly0) * P + __builtin_amdgcn_readlane(m_lx, j + r) - lx0;
-    const int k = __builtin_amdgcn_readlane(m_k, j + r);
-#pragma unroll
-    for (int c = 0; c < NP; ++c) {
-      const float2 a = vis[static_cast<size_t>(k) * NP + c];
-      v[r][c] = make_float2(ldexpf(a.x, ex), ldexpf(a.y, ex));
-    }
-  }
-  // one tap of the footprint for all R rows; off = the tap's sub-grid word for the run's first row
-  auto tap_rows = [&](int off, const float2 (&tap)[NQ * NP]) {
-    // an opaque copy of the cursor: the compiler would otherwise keep one strength-reduced address
-    // per row and word, each stepped on every pass
-    asm volatile("" : "+v"(off));
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        float yr = 0.0f, yi = 0.0f;
-#pragma unroll
-        for (int c = 0; c < NP; ++c) {
-          const float2 a = tap[q * NP + c];
-          yr = fmaf(a.x, v[r][c].x, fmaf(-a.y, v[r][c].y, yr));
-          yi = fmaf(a.x, v[r][c].y, fmaf(a.y, v[r][c].x, yi));
-        }
-        unsigned long long* cell = lds + q * WP + off + d[r];
-        atomicAdd(cell, pack_pair(floor_to_int(yr), floor_to_int(yi)));
-        // fract(y) = y - floor(y) in [0, 1), truncated to f bits: the residual is below one fine unit
-        atomicAdd(cell + fine_off, pack_fine(static_cast<unsigned>(__builtin_amdgcn_fractf(yr) * fscale),
-                                             static_cast<unsigned>(__builtin_amdgcn_fractf(yi) * fscale)));
-      }
-    }
-  };
-  // Lane u takes taps u, u + 64, ... in passes of 64; after the full passes, a last pass takes the
-  // SS mod 64 taps left (if any) on the lanes that have one.  The taps of the next pass are loaded
-  // while this pass's rows are computed (two buffers, alternating; loads past the last tap read tap
-  // SS - 1 and are not used), in a loop without branches so that each wait covers only the buffer
-  // it needs.  When S divides 64 the footprint advances by whole rows and the cursor needs no wrap.
-  TapCursor cur(lane, ly0, lx0, inv_s, S, P);
-  const int full = SS >> 6;
-  const bool tail_lane = lane < SS - (full << 6);
-  const uint32_t b_last = static_cast<uint32_t>(SS - 1) * TB;
-  const uint32_t b0 = static_cast<uint32_t>(lane) * TB;
-  auto load_pass = [&](int p, float2 (&tap)[NQ * NP]) {
-    tc.load_at(min(b0 + static_cast<uint32_t>(p) * (64 * TB), b_last), tap);
-  };
-  auto run = [&](auto advance) {
-    if constexpr (PF) {
-      float2 ta[NQ * NP], tb[NQ * NP];
-      load_pass(0, ta);
-      int p = 0;
-      for (; p + 2 <= full; p += 2) {
-        load_pass(p + 1, tb);
-        tap_rows(cur.off, ta);
-        advance();
-        load_pass(p + 2, ta);
-        tap_rows(cur.off, tb);
-        advance();
-      }
-      if (p < full) {  // one full pass left, in ta; the tail pass (if any) goes to tb
-        load_pass(p + 1, tb);
-        tap_rows(cur.off, ta);
-        advance();
-        if (tail_lane) tap_rows(cur.off, tb);
-      } else if (tail_lane) {  // ta holds the tail pass
-        tap_rows(cur.off, ta);
-      }
-    } else {
-      float2 ta[NQ * NP];
-      for (int p = 0; p < full; ++p) {
-        load_pass(p, ta);
-        tap_rows(cur.off, ta);
-        advance();
-      }
-      if (tail_lane) {
-        load_pass(full, ta);
-        tap_rows(cur.off, ta);
-      }
-    }
-  };
-  if (step.dt == 0) {
-    run([&]() { cur.off += step.doff; });
-  } else {
-    run([&]() { cur.advance(step); });
-  }
+typedef float MfmaF4 __attribute__((ext_vector_type(4)));
+
+// Waves per SIMD the shared-tap kernels are compiled for: two workgroups of 16 waves share a CU (each
+// holds at most half of its LDS with one output plane), which takes 64 vector registers.
+constexpr int shared_waves_per_simd(int nw, int nq) { return nw == 16 && nq == 1 ? 8 : 1; }
+
+// A run of up to 8 rows of one phase as a wave holds it, and one tap (per lane) of the footprint
+// applied to all its rows.  Rows are taken in pairs on the matrix cores (v_mfma_f32_4x4x1: the outer
+// product of four coefficients, two rows x (re, im), with 64 taps), an odd last row on the vector
+// ALU.  The order of the products and their rounding are those of a chain of float FMAs either way.
+// What limits this loop is how often a wave can issue (5 to 8 cycles from one of its instructions to
+// the next, whatever the unit), so it wants few instructions and many waves: the rows' offsets and
+// the odd row's values stay scalar, and the state fits 64 vector registers (8 waves per SIMD).
+constexpr int kGridRun = 8;
+typedef __attribute__((address_space(3))) unsigned long long LdsWord;
+
+__device__ __forceinline__ void lds_add(uint32_t at, unsigned long long v) {
+  __hip_atomic_fetch_add(reinterpret_cast<LdsWord*>(at), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+
+template <int NP, int NQ>
+struct GridRun {
+  uint32_t d[kGridRun], d_odd;  // the rows' sub-grid byte offsets
+  float a_im[NP], a_re[NP];     // lane 4p + i: component i & 1 of row 2p + (i >> 1), times Im and Re of tap c
+  float2 v[NP];                 // the last row of an odd run
+  uint32_t im_off, plane_bytes; // from a value's real word to its imaginary one, from a plane to the next
+
+  // rows j .. j + count - 1 of the wave's 64-row block (lane i of m_off and mv: row i)
+  __device__ __forceinline__ void set(int j, int count, int m_off, const float2 (&mv)[NP], int lane) {
+#pragma unroll
+    for (int r = 0; r < kGridRun; ++r) d[r] = static_cast<uint32_t>(__builtin_amdgcn_readlane(m_off, (j + r) & 63));
+    if (count > 1) {
+      const int src = ((j + (lane >> 1)) & 63) << 2;
+#pragma unroll
+      for (int c = 0; c < NP; ++c) {
+        const float re = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mv[c].x)));
+        const float im = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mv[c].y)));
+        a_im[c] = (lane & 1) ? re : -im;
+        a_re[c] = (lane & 1) ? im : re;
+      }
+    }
+    if (count & 1) {
+      const int o = j + count - 1;
+      d_odd = static_cast<uint32_t>(__builtin_amdgcn_readlane(m_off, o));
+#pragma unroll
+      for (int c = 0; c < NP; ++c) {
+        v[c].x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mv[c].x), o));
+        v[c].y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mv[c].y), o));
+      }
+    }
+  }
+
+  __device__ __forceinline__ void add(uint32_t at, float yr, float yi) const {
+    lds_add(at, fixed_bits(yr));
+    lds_add(at + im_off, fixed_bits(yi));
+  }
+
+  // PAIRS row pairs from pair P0 on; at = the tap's byte offset in the footprint
+  template <int P0, int PAIRS>
+  __device__ __forceinline__ void pairs(uint32_t at, const float2 (&tap)[NQ * NP]) const {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      MfmaF4 y0 = {0.0f, 0.0f, 0.0f, 0.0f}, y1 = y0;
+#pragma unroll
+      for (int c = 0; c < NP; ++c) {
+        const float2 t = tap[q * NP + c];
+        y0 = __builtin_amdgcn_mfma_f32_4x4x1f32(a_im[c], t.y, y0, 4, P0, 0);
+        if constexpr (PAIRS > 1) y1 = __builtin_amdgcn_mfma_f32_4x4x1f32(a_im[c], t.y, y1, 4, P0 + 1, 0);
+        y0 = __builtin_amdgcn_mfma_f32_4x4x1f32(a_re[c], t.x, y0, 4, P0, 0);
+        if constexpr (PAIRS > 1) y1 = __builtin_amdgcn_mfma_f32_4x4x1f32(a_re[c], t.x, y1, 4, P0 + 1, 0);
+      }
+      add(at + d[2 * P0], y0[0], y0[1]);
+      add(at + d[2 * P0 + 1], y0[2], y0[3]);
+      if constexpr (PAIRS > 1) {
+        add(at + d[2 * P0 + 2], y1[0], y1[1]);
+        add(at + d[2 * P0 + 3], y1[2], y1[3]);
+      }
+      at += plane_bytes;
+    }
+  }
+
+  __device__ __forceinline__ void odd(uint32_t at, const float2 (&tap)[NQ * NP]) const {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      float yr = 0.0f, yi = 0.0f;
+#pragma unroll
+      for (int c = 0; c < NP; ++c) {
+        const float2 t = tap[q * NP + c];
+        yr = fmaf(t.x, v[c].x, fmaf(-t.y, v[c].y, yr));
+        yi = fmaf(t.x, v[c].y, fmaf(t.y, v[c].x, yi));
+      }
+      add(at + d_odd, yr, yi);
+      at += plane_bytes;
+    }
+  }
+
+  __device__ __forceinline__ void apply(int count, uint32_t at, const float2 (&tap)[NQ * NP]) const {
+    if (count >= 4) {
+      pairs<0, 2>(at, tap);
+      if (count == 8)
+        pairs<2, 2>(at, tap);
+      else if (count >= 6)
+        pairs<2, 1>(at, tap);
+    } else if (count >= 2) {
+      pairs<0, 1>(at, tap);
+    }
+    if (count & 1) odd(at, tap);
+  }
+};
 
 // FIXED: the reproducible mode's flush.  The item's values are exact integers at the scale
-// 2^(e + f); they are moved to the launch-wide scale of the 64-bit accumulators by a shift (exact
-// when it is a left shift, a floor when right) and added with integer atomics.
-// TWO_BUFFERS: the single-plan launches take two tap buffers where the registers hold them; the
-// batched launch keeps one (measured faster there)
-template <int NP, typename TapT, int NW, int NQ = NP, bool FIXED = false, bool TWO_BUFFERS = true>
+// 2^(e + kFixedBits); they are moved to the launch-wide scale of the 64-bit accumulators by a shift
+// (exact when it is a left shift, a floor when right) and added with integer atomics.
+template <int NP, typename TapT, int NW, int NQ = NP, bool FIXED = false>
 __device__ __forceinline__ void grid_item_shared(const Item it, const int2* __restrict__ fine,
                                                  const int32_t* __restrict__ perm, const float2* __restrict__ vis,
                                                  const TapT* __restrict__ table, const PlaneInfo* __restrict__ planes,
                                                  const float* __restrict__ kbound, int os, int n,
                                                  float2* __restrict__ grid, int flags, int sub_bytes, float* lds_f,
                                                  int q0 = 0, FixedSink fx = FixedSink{nullptr, nullptr}) {
-  // [coarse | fine][q][W][P] packed (re, im) words; sub_bytes covers both
+  // [re | im][q][W][P] fixed-point words; sub_bytes covers both
   unsigned long long* lds = reinterpret_cast<unsigned long long*>(lds_f);
+  const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)lds_f));
   float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(lds_f) + sub_bytes);  // [NW]
   const PlaneInfo pl = planes[it.plane];
   const int S = pl.support, W = pl.width, P = pl.pitch, WP = W * P, SS = S * S, half = S * os / 2;
-  const int fine_off = NQ * WP;
-  const float inv_s = 1.0f / static_cast<float>(S);
-  for (int i = threadIdx.x; i < 2 * fine_off; i += NW * 64) lds[i] = 0ull;
-  // largest row sum of |Re V_c| + |Im V_c| over the item (a maximum: the same in every thread and
-  // for any partition of the rows)
-  float m1 = 0.0f;
-  constexpr int kRowsPerPass = 2;  // rows per thread whose loads are in flight together
-  for (int i0 = it.start + static_cast<int>(threadIdx.x); i0 < it.end; i0 += kRowsPerPass * NW * 64) {
-    int k[kRowsPerPass];
-#pragma unroll
-    for (int u = 0; u < kRowsPerPass; ++u) {
-      const int i = i0 + u * NW * 64;
-      k[u] = i < it.end ? perm[i] : -1;
-    }
-    float2 a[kRowsPerPass][NP];
-#pragma unroll
-    for (int u = 0; u < kRowsPerPass; ++u) {
-      const size_t kk = static_cast<size_t>(k[u] < 0 ? 0 : k[u]);  // row 0 stands in, unused
-#pragma unroll
-      for (int c = 0; c < NP; ++c) a[u][c] = vis[kk * NP + c];
-    }
-#pragma unroll
-    for (int u = 0; u < kRowsPerPass; ++u) {
-      if (k[u] < 0) continue;
-      float a1 = 0.0f;
-#pragma unroll
-      for (int c = 0; c < NP; ++c) a1 += fabsf(a[u][c].x) + fabsf(a[u][c].y);
-      m1 = (a1 > m1 || a1 != a1) ? a1 : m1;  // a NaN row wins, so a non-finite item is recognised
-    }
-  }
+  const int im_words = NQ * WP;
+  const float inv_s = 1.0f / static_cast<float>(S), inv_os = 1.0f / static_cast<float>(os);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rows = it.end - it.start;
+  // wave w takes a contiguous run of the item's rows; 64 at a time, lane i holds row i's sub-grid
+  // byte offset, kernel phase and visibility
+  const int per = (rows + NW - 1) / NW;
+  const int w0 = it.start + wave * per, w1 = min(it.end, w0 + per);
+  int m_off = 0, m_ph = -1;
+  float2 mv[NP];
+  auto load_block = [&](int blk) {
+    const int mine = blk + lane;
+    m_off = 0;
+    m_ph = -1;
+#pragma unroll
+    for (int c = 0; c < NP; ++c) mv[c] = make_float2(0.0f, 0.0f);
+    if (mine < w1) {
+      const size_t k = static_cast<size_t>(perm[mine]);
+#pragma unroll
+      for (int c = 0; c < NP; ++c) mv[c] = vis[k * NP + c];
+      const int2 f = fine[mine];
+      // kept rows have x0, y0 >= 0: their quotients by os, exact in float (at most 2^18 + 1/2 over os)
+      const int x0 = static_cast<int>((static_cast<float>(f.x - half + os) + 0.5f) * inv_os);
+      const int y0 = static_cast<int>((static_cast<float>(f.y - half + os) + 0.5f) * inv_os);
+      m_off = ((y0 - it.oy) * P + x0 - it.ox) * 8;
+      m_ph = (y0 * os - f.y + half - 1) * os + (x0 * os - f.x + half - 1);
+    }
+  };
+  // largest row sum of |Re V_c| + |Im V_c| over the item (a maximum: the same in every thread and
+  // for any partition of the rows); a NaN row wins, so a non-finite item is recognised
+  float m1 = 0.0f;
+  auto take_max = [&]() {
+    float a1 = 0.0f;
+#pragma unroll
+    for (int c = 0; c < NP; ++c) a1 += fabsf(mv[c].x) + fabsf(mv[c].y);
+    m1 = (a1 > m1 || a1 != a1) ? a1 : m1;
+  };
+  for (int blk = w0 + (w1 > w0 ? (w1 - w0 - 1) / 64 * 64 : 0); blk >= w0; blk -= 64) {
+    load_block(blk);  // last block first: the first stays in the registers
+    take_max();
+  }
+  for (int i = threadIdx.x; i < im_words; i += NW * 64) reinterpret_cast<ulonglong2*>(lds)[i] = make_ulonglong2(0, 0);
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     const float other = __shfl_xor(m1, o, 64);
@@ -697,7 +718,6 @@ __device__ __forceinline__ void grid_item_shared(const Item it, const int2* __re
     finite = finite && part[w] == part[w] && part[w] <= 3.0e38f;
     mrow = fmaxf(mrow, part[w]);
   }
-  const int rows = it.end - it.start;
   // in float64, so that only non-finite inputs (not a bound beyond the float range) stop the item
   const double b = static_cast<double>(kmax) * static_cast<double>(mrow) * static_cast<double>(rows);
   int ex = 0;
@@ -706,50 +726,66 @@ __device__ __forceinline__ void grid_item_shared(const Item it, const int2* __re
   } else if (b > 0.0) {
     int e2 = 0;
     frexp(b, &e2);  // b < 2^e2
-    ex = 29 - e2;
+    ex = 28 - e2;
   }
-  int lg = 0;  // ceil(log2(rows))
-  while ((1 << lg) < rows && lg < 30) ++lg;
-  const int fbits = min(20, 30 - lg);
-  const float fscale = ldexpf(1.0f, fbits);
   const FootStep step(S, P);
-  constexpr bool kPF = TWO_BUFFERS && NW * NQ <= 16;  // and room for them in the registers
-  const int per = (rows + NW - 1) / NW;
-  const int w0 = it.start + wave * per, w1 = min(it.end, w0 + per);
+  const TapCursor start(lane, 0, 0, inv_s, S, P);
+  // the plane's table rows q0 .. of phase 0; a phase is phase_bytes further on (less than 2^27 in all)
+  const TapChunks<NQ * NP, TapT> tc(table + pl.offset + static_cast<size_t>(q0) * NP * SS, SS);
+  const uint32_t phase_bytes = static_cast<uint32_t>(NP * NP * SS) * static_cast<uint32_t>(sizeof(TapT));
+  constexpr uint32_t TB = TapChunks<NQ * NP, TapT>::kTapBytes;
+  const int full = SS >> 6, passes = (SS + 63) >> 6;
+  const bool tail_lane = lane < SS - (full << 6);
+  const uint32_t b_last = static_cast<uint32_t>(SS - 1) * TB, b0 = static_cast<uint32_t>(lane) * TB;
+  GridRun<NP, NQ> gr;
+  gr.im_off = static_cast<uint32_t>(im_words) * 8u;
+  gr.plane_bytes = static_cast<uint32_t>(WP) * 8u;
+  asm volatile("" : "+v"(gr.im_off));
   for (int blk = w0; blk < w1 && finite; blk += 64) {
-    const int mine = blk + lane;
-    int m_ly = 0, m_lx = 0, m_ph = -1, m_k = 0;
-    if (mine < w1) {
-      const int2 f = fine[mine];
-      const int x0 = ceil_div_i(f.x - half + 1, os), y0 = ceil_div_i(f.y - half + 1, os);
-      m_ly = y0 - it.oy;
-      m_lx = x0 - it.ox;
-      m_ph = (y0 * os - f.y + half - 1) * os + (x0 * os - f.x + half - 1);
-      m_k = perm[mine];
-    }
+    if (blk != w0) load_block(blk);
+#pragma unroll
+    for (int c = 0; c < NP; ++c) mv[c] = make_float2(ldexpf(mv[c].x, ex), ldexpf(mv[c].y, ex));
     const int nrow = min(64, w1 - blk);
-    for (int j = 0; j < nrow;) {
-      const int ph = __builtin_amdgcn_readlane(m_ph, j);
-      int run = 1;  // rows from j on with the same phase, up to 8
-      while (run < 8 && j + run < nrow && __builtin_amdgcn_readlane(m_ph, j + run) == ph) ++run;
-      run = __builtin_amdgcn_readfirstlane(run);
-      const TapT* pt = table + pl.offset + (static_cast<size_t>(ph) * NP * NP + q0 * NP) * SS;
-      if (run == 8) {
-        grid_rows_shared<NP, TapT, 8, NQ, kPF>(lds, fine_off, pt, j, m_ly, m_lx, m_k, vis, S, SS, P, WP, inv_s, step, lane,
-                                               ex, fscale);
-      } else if (run >= 4) {
-        grid_rows_shared<NP, TapT, 4, NQ, kPF>(lds, fine_off, pt, j, m_ly, m_lx, m_k, vis, S, SS, P, WP, inv_s, step, lane,
-                                               ex, fscale);
-        run = 4;
-      } else if (run >= 2) {
-        grid_rows_shared<NP, TapT, 2, NQ, kPF>(lds, fine_off, pt, j, m_ly, m_lx, m_k, vis, S, SS, P, WP, inv_s, step, lane,
-                                               ex, fscale);
-        run = 2;
-      } else {
-        grid_rows_shared<NP, TapT, 1, NQ, kPF>(lds, fine_off, pt, j, m_ly, m_lx, m_k, vis, S, SS, P, WP, inv_s, step, lane,
-                                               ex, fscale);
+    // first rows of the runs of one phase (the lanes past the last row, phase -1, start one too)
+    const int before = __shfl_up(m_ph, 1, 64);
+    const uint64_t starts = __ballot(lane == 0 || m_ph != before);
+    auto run_at = [&](int j) {  // rows of the run at row j, at most kGridRun
+      const uint64_t rest = (starts >> j) >> 1;
+      return min(rest ? __builtin_ctzll(rest) + 1 : 64 - j, kGridRun);
+    };
+    // byte offset of row j's phase (of row 0's past the last row)
+    auto phase_at = [&](int j) {
+      return static_cast<uint32_t>(__builtin_amdgcn_readlane(m_ph, j < nrow ? j : 0)) * phase_bytes;
+    };
+    // The wave walks its runs in steps of 64 taps: lane u takes taps u, u + 64, ... of the footprint,
+    // the last step of a run the taps left, on the lanes that have one.  Two tap buffers: a step
+    // requests the taps of the one after it, of its own run or the first of the next (loads past the
+    // last tap read tap SS - 1 and are not used), before it computes its rows.
+    int j = 0, pass = 0, run = run_at(0);
+    uint32_t phase = phase_at(0);
+    TapCursor cur = start;
+    auto take_step = [&](const float2 (&tap)[NQ * NP], float2 (&tap_next)[NQ * NP]) {
+      const bool last = pass + 1 == passes;
+      const int j2 = last ? j + run : j, pass2 = last ? 0 : pass + 1;
+      if (last) phase = phase_at(j2);
+      tc.load_at(min(b0 + static_cast<uint32_t>(pass2) * (64 * TB), b_last) + phase, tap_next);
+      if (pass == 0) {
+        gr.set(j, run, m_off, mv, lane);
+        cur = start;
       }
-      j += run;
+      if (pass < full || tail_lane) gr.apply(run, lds_base + static_cast<uint32_t>(cur.off) * 8u, tap);
+      if (step.dt == 0)
+        cur.off += step.doff;
+      else
+        cur.advance(step);
+      pass = pass2;
+      j = j2;
+      if (last) run = run_at(j2 & 63);
+      return j < nrow;
+    };
+    float2 ta[NQ * NP], tb[NQ * NP];
+    tc.load_at(min(b0, b_last) + phase, ta);
+    while (take_step(ta, tb) && take_step(tb, ta)) {
     }
   }
   __syncthreads();
@@ -757,20 +793,16 @@ __device__ __forceinline__ void grid_item_shared(const Item it, const int2* __re
   const size_t pstride = static_cast<size_t>(n) * n;
   if constexpr (FIXED) {
     if (!finite) return;  // the reproducible mode requires finite inputs
-    const int sh = __builtin_amdgcn_readfirstlane(*fx.exp) - ex - fbits;
-    for (int idx = threadIdx.x; idx < W * W; idx += NW * 64) {
-      const int y = idx / W, x = idx - y * W;
+    const int sh = __builtin_amdgcn_readfirstlane(*fx.exp) - ex - kFixedBits;
+    for (int y = wave; y < min(W, n - it.oy); y += NW)
+    for (int x = lane; x < min(W, n - it.ox); x += 64) {
       const int X = it.ox + x, Y = it.oy + y;
-      if (X >= n || Y >= n) continue;
       const int l = y * P + x;
       const bool neg = shift && ((X + Y) & 1);
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
-        const unsigned long long cw = lds[q * WP + l], fw = lds[fine_off + q * WP + l];
-        if ((cw | fw) == 0ull) continue;
-        const int2 h = unpack_pair(cw), f = unpack_pair(fw);
-        long long v[2] = {static_cast<long long>(static_cast<unsigned long long>(static_cast<long long>(h.x)) << fbits) + f.x,
-                          static_cast<long long>(static_cast<unsigned long long>(static_cast<long long>(h.y)) << fbits) + f.y};
+        const long long v[2] = {fixed_value(lds[q * WP + l]), fixed_value(lds[im_words + q * WP + l])};
+        if ((v[0] | v[1]) == 0) continue;
         const size_t o = (q0 + q) * pstride + static_cast<size_t>(Y) * n + X;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
@@ -786,10 +818,9 @@ __device__ __forceinline__ void grid_item_shared(const Item it, const int2* __re
     }
     return;
   }
-  for (int idx = threadIdx.x; idx < W * W; idx += NW * 64) {
-    const int y = idx / W, x = idx - y * W;
+  for (int y = wave; y < min(W, n - it.oy); y += NW)
+  for (int x = lane; x < min(W, n - it.ox); x += 64) {
     const int X = it.ox + x, Y = it.oy + y;
-    if (X >= n || Y >= n) continue;
     const int l = y * P + x;
     const float sg = (shift && ((X + Y) & 1)) ? -1.0f : 1.0f;
 #pragma unroll
@@ -800,20 +831,17 @@ __device__ __forceinline__ void grid_item_shared(const Item it, const int2* __re
         unsafeAtomicAdd(gp + 1, __int_as_float(0x7fc00000));
         continue;
       }
-      const unsigned long long cw = lds[q * WP + l], fw = lds[fine_off + q * WP + l];
-      if ((cw | fw) != 0ull) {
-        const int2 h = unpack_pair(cw), f = unpack_pair(fw);
-        const double re = ldexp(static_cast<double>(h.x) + ldexp(static_cast<double>(f.x), -fbits), -ex);
-        const double im = ldexp(static_cast<double>(h.y) + ldexp(static_cast<double>(f.y), -fbits), -ex);
-        unsafeAtomicAdd(gp, sg * static_cast<float>(re));
-        unsafeAtomicAdd(gp + 1, sg * static_cast<float>(im));
+      const long long vr = fixed_value(lds[q * WP + l]), vi = fixed_value(lds[im_words + q * WP + l]);
+      if ((vr | vi) != 0) {
+        unsafeAtomicAdd(gp, sg * static_cast<float>(ldexp(static_cast<double>(vr), -ex - kFixedBits)));
+        unsafeAtomicAdd(gp + 1, sg * static_cast<float>(ldexp(static_cast<double>(vi), -ex - kFixedBits)));
       }
     }
   }
 }
 
 template <int NP, typename TapT, int NW, int NQ = NP>
-__global__ __launch_bounds__(NW * 64) void grid_shared_kernel(const Item* __restrict__ items,
+__global__ __launch_bounds__(NW * 64, shared_waves_per_simd(NW, NQ)) void grid_shared_kernel(const Item* __restrict__ items,
                                                               const int2* __restrict__ fine,
                                                               const int32_t* __restrict__ perm,
                                                               const float2* __restrict__ vis,
@@ -830,11 +858,11 @@ __global__ __launch_bounds__(NW * 64) void grid_shared_kernel(const Item* __rest
                                      sub_bytes, lds_f, part * NQ);
 }
 
-// Reproducible gridding with the shared-tap kernel: 8 waves per workgroup and a number of output
+// Reproducible gridding with the shared-tap kernel: 16 waves per workgroup and a number of output
 // planes per workgroup that depends only on the kernel set, so every item's exact sub-grid, and the
 // 64-bit sums of all items, are the same bits whatever the plan's launch settings.
 template <int NP, typename TapT, int NQ>
-__global__ __launch_bounds__(512) void grid_shared_fixed_kernel(const Item* __restrict__ items,
+__global__ __launch_bounds__(1024, shared_waves_per_simd(16, NQ)) void grid_shared_fixed_kernel(const Item* __restrict__ items,
                                                                 const int2* __restrict__ fine,
                                                                 const int32_t* __restrict__ perm,
                                                                 const float2* __restrict__ vis,
@@ -844,7 +872,7 @@ __global__ __launch_bounds__(512) void grid_shared_fixed_kernel(const Item* __re
                                                                 int flags, int sub_bytes, FixedSink fx) {
   extern __shared__ float lds_f[];
   const int item = blockIdx.x / (NP / NQ), part = blockIdx.x - item * (NP / NQ);
-  grid_item_shared<NP, TapT, 8, NQ, true>(items[item], fine, perm, vis, table, planes, kbound, os, n, nullptr, flags,
+  grid_item_shared<NP, TapT, 16, NQ, true>(items[item], fine, perm, vis, table, planes, kbound, os, n, nullptr, flags,
                                           sub_bytes, lds_f, part * NQ, fx);
 }
 
@@ -961,7 +989,7 @@ __global__ __launch_bounds__(NW * 64) void grid_banded_batch(const FieldArgs* __
 // The shared-tap gridder over a batch: workgroup b takes part b mod (NP / NQ) (its NQ output
 // planes) of the (field, item) pair work[b / (NP / NQ)].
 template <int NP, typename TapT, int NW, int NQ>
-__global__ __launch_bounds__(NW * 64) void grid_shared_batch(const FieldArgs* __restrict__ fields,
+__global__ __launch_bounds__(NW * 64, shared_waves_per_simd(NW, NQ)) void grid_shared_batch(const FieldArgs* __restrict__ fields,
                                                              const int2* __restrict__ work, int flags,
                                                              int sub_bytes) {
   extern __shared__ float lds_f[];
@@ -969,7 +997,7 @@ __global__ __launch_bounds__(NW * 64) void grid_shared_batch(const FieldArgs* __
   if (wr.x < 0) return;
   const int part = blockIdx.x % (NP / NQ);
   ConstFieldArgs& fa = ((ConstFieldArgs*)fields)[wr.x];
-  grid_item_shared<NP, TapT, NW, NQ, false, false>(fa.items[wr.y], fa.fine, fa.perm, fa.vis,
+  grid_item_shared<NP, TapT, NW, NQ>(fa.items[wr.y], fa.fine, fa.perm, fa.vis,
                                                    static_cast<const TapT*>(fa.table), fa.planes, fa.kbound, fa.os,
                                                    fa.n, fa.grid, flags, sub_bytes, lds_f, part * NQ);
 }
@@ -1552,7 +1580,7 @@ hipError_t run_grid_fixed(const pg_plan* p, const pg_kernels* k, const float2* v
     auto launch = [&](auto fn) -> hipError_t {
       hipError_t e2 = allow_lds(fn, sub + kSharedScratch);
       if (e2 != hipSuccess) return e2;
-      hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(p->n_items * (NP / nq))), dim3(512), sub + kSharedScratch, s,
+      hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(p->n_items * (NP / nq))), dim3(1024), sub + kSharedScratch, s,
                          p->items.as<Item>(), p->fine.as<int2>(), p->perm.as<int32_t>(), vis, k->table.as<TapT>(),
                          k->planes.as<PlaneInfo>(), k->kbound.as<float>(), k->os, k->n, flags, static_cast<int>(sub),
                          FixedSink{acc, exp});
