@@ -1268,7 +1268,9 @@ __global__ void zero_dropped(const int32_t* __restrict__ perm, int64_t n_kept, i
   for (int c = 0; c < np; ++c) vis_out[k * np + c] = make_float2(0.0f, 0.0f);
 }
 
-__global__ void fill_zero_kernel(uint64_t* __restrict__ p, size_t n) {
+// n 8-byte words, then the 4 bytes behind them when `half` (an odd count of 4-byte values)
+__global__ void fill_zero_kernel(uint64_t* __restrict__ p, size_t n, int half) {
+  if (half && blockIdx.x == 0 && threadIdx.x == 0) *reinterpret_cast<uint32_t*>(p + n) = 0;
   for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<size_t>(gridDim.x) * blockDim.x)
     p[i] = 0;
@@ -1536,9 +1538,9 @@ hipError_t launch_batch_degrid(const pg_batch* b, int flags, hipStream_t s) {
 
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   const size_t n = bytes / 8;
-  if (n == 0) return hipSuccess;
-  const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n + 255) / 256, 16384));
-  hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, s, static_cast<uint64_t*>(p), n);
+  if (bytes < 4) return hipSuccess;
+  const unsigned blocks = static_cast<unsigned>(std::max<size_t>(1, std::min<size_t>((n + 255) / 256, 16384)));
+  hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, s, static_cast<uint64_t*>(p), n, bytes & 4 ? 1 : 0);
   return hipGetLastError();
 }
 
