@@ -18,8 +18,22 @@ hipError_t mlp_silu_back(const float* gact, const float* z, int64_t n, float* gp
 hipError_t mlp_loss(const float* y, const float* t, int64_t cols, int batch, float* grad, uint16_t* grad_bf,
                     float* loss, hipStream_t s);
 hipError_t mlp_colsum(const float* g, int64_t rows, int64_t cols, float* out, hipStream_t s);
-hipError_t mlp_adam(float* w, uint16_t* w_bf, const float* g, float* m, float* v, int64_t n, float lr, double b1,
-                    double b2, double eps, int64_t step, hipStream_t s);
+// One parameter array of an Adam step, [rows][cols] (a bias: one row): float32 masters, gradient and
+// moments; for weights also the bf16 copy and its transpose [cols][rows] (NULL for a bias).
+struct AdamArray {
+  float* w;
+  const float* g;
+  float *m, *v;
+  uint16_t *w_bf, *w_bft;
+  int64_t rows, cols;
+  uint32_t first_tile;  // set by mlp_adam
+};
+constexpr int kAdamMax = 34;  // weights and bias of 16 hidden layers and the output layer
+struct AdamArrays {
+  int count;
+  AdamArray array[kAdamMax];
+};
+hipError_t mlp_adam(AdamArrays p, float lr, double b1, double b2, double eps, int64_t step, hipStream_t s);
 hipError_t mlp_to_bf16(const float* x, int64_t n, uint16_t* out, hipStream_t s);
 hipError_t mlp_init_uniform(float* w, int64_t n, uint64_t seed, float a, hipStream_t s);
 struct CellScale {

@@ -171,16 +171,16 @@ int pg_mlp_train_step(pg_mlp* m, const float* x, const float* target, int32_t ba
   }
   if (update) {
     m->step += 1;
+    pg::AdamArrays p;
+    p.count = 0;
     for (int l = 0; l < L; ++l) {
       auto& ly = m->layers[l];
-      const int64_t nw = m->dims[l] * m->dims[l + 1];
-      PGM_HIP(pg::mlp_adam(ly.w.as<float>(), ly.w_bf.as<uint16_t>(), ly.gw.as<float>(), ly.mw.as<float>(),
-                           ly.vw.as<float>(), nw, lr, 0.9, 0.999, 1e-8, m->step, s), "adam");
-      PGM_HIP(pg::mlp_transpose_bf16(ly.w_bf.as<uint16_t>(), m->dims[l], m->dims[l + 1], ly.w_bft.as<uint16_t>(), s),
-              "adam transpose");
-      PGM_HIP(pg::mlp_adam(ly.b.as<float>(), nullptr, ly.gb.as<float>(), ly.mb.as<float>(), ly.vb.as<float>(),
-                           m->dims[l + 1], lr, 0.9, 0.999, 1e-8, m->step, s), "adam");
+      p.array[p.count++] = {ly.w.as<float>(), ly.gw.as<float>(), ly.mw.as<float>(), ly.vw.as<float>(),
+                            ly.w_bf.as<uint16_t>(), ly.w_bft.as<uint16_t>(), m->dims[l], m->dims[l + 1], 0};
+      p.array[p.count++] = {ly.b.as<float>(), ly.gb.as<float>(), ly.mb.as<float>(), ly.vb.as<float>(),
+                            nullptr, nullptr, 1, m->dims[l + 1], 0};
     }
+    PGM_HIP(pg::mlp_adam(p, lr, 0.9, 0.999, 1e-8, m->step, s), "adam");
   }
   if (loss_out) PGM_HIP(hipMemcpyAsync(loss_out, m->loss.p, 4, hipMemcpyDeviceToDevice, s), "copy loss");
   return PG_OK;
