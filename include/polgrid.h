@@ -350,11 +350,10 @@ int pg_normalise_at(float* img, int64_t count, int64_t ref_index, void* stream);
 
 /* pg_hogbom without any device allocation, for callers that cannot allocate: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and
- * kernels as pg_hogbom; the scratch pg_hogbom allocates per call (iteration state and one 64-bit
- * peak slot per iteration) is instead a fixed device array of the library, 256 + 8 x
- * PG_HOGBOM_STATIC_MAX_ITER bytes (about 512 KiB) on each GPU it runs on, held until the process
- * ends.  Every call on one GPU shares that GPU's array, so calls that overlap on one GPU (other
- * streams or threads) race; each call clears the part it uses before its first iteration.  Only
+ * kernels as pg_hogbom; the scratch pg_hogbom allocates per call (iteration state and two sets of
+ * tile records) is instead a fixed device array of the library, about 64 KiB on each GPU it runs on,
+ * held until the process ends.  Every call on one GPU shares that GPU's array, so calls that overlap on one GPU (other
+ * streams or threads) race; each call writes the part it uses before its first iteration.  Only
  * kernel launches are enqueued (no hipMalloc, hipFree, memset or copy).  Errors: as pg_hogbom, and
  * PG_EINVAL when max_iter exceeds PG_HOGBOM_STATIC_MAX_ITER. */
 #define PG_HOGBOM_STATIC_MAX_ITER 65536

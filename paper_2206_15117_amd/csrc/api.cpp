@@ -669,7 +669,7 @@ int pg_hogbom(float* residual, const float* psf, const uint8_t* mask, int32_t n,
   hipStream_t s = static_cast<hipStream_t>(stream);
   try {
     DevBuf scratch;
-    if (!scratch.alloc(256 + 8 * static_cast<size_t>(std::max(max_iter, 1)), s))
+    if (!scratch.alloc(hogbom_scratch_bytes(), s))
       return fail(PG_ENOMEM, "device allocation failed in hogbom");
     PG_HIP(launch_hogbom(residual, psf, mask, n, npol, gain, threshold, patch, max_iter, comp_pos, comp_val, model,
                          n_comp, scratch.p, s),
@@ -734,7 +734,7 @@ int pg_hogbom_noalloc(float* residual, const float* psf, const uint8_t* mask, in
   void* scratch = nullptr;
   size_t bytes = 0;
   PG_HIP(hogbom_static_scratch(&scratch, &bytes), "hogbom_noalloc scratch address");
-  if (256 + 8 * static_cast<size_t>(std::max(max_iter, 1)) > bytes) return fail(PG_EINVAL, "scratch too small");
+  if (hogbom_scratch_bytes() > bytes) return fail(PG_EINVAL, "scratch too small");
   PG_HIP(launch_hogbom(residual, psf, mask, n, npol, gain, threshold, patch, max_iter, comp_pos, comp_val, model,
                        n_comp, scratch, static_cast<hipStream_t>(stream)),
          "hogbom_noalloc");

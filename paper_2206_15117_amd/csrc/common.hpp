@@ -209,6 +209,8 @@ hipError_t launch_grid_fixed(const pg_plan* p, const pg_kernels* k, const float2
                              void* scratch, hipStream_t s);
 hipError_t launch_taper(const pg_kernels* k, const void* in, void* out, int direction, double weight_sum,
                         hipStream_t s);
+// Minor cycle with caller-provided scratch of hogbom_scratch_bytes().
+size_t hogbom_scratch_bytes();
 hipError_t launch_hogbom(float* residual, const float* psf, const uint8_t* mask, int n, int npol, float gain,
                          float threshold, int patch, int max_iter, int32_t* comp_pos, float* comp_val, float* model,
                          int32_t* n_comp, void* scratch, hipStream_t s);
