@@ -179,21 +179,25 @@ hipError_t launch_zgemm_nn(int batch, int m, int n, int k, const double2* a, int
 hipError_t launch_pack(const double2* t, int support, int os, int nqc, int storage, void* table, hipStream_t s);
 
 // Plan (plan.hip)
-hipError_t launch_plan_keys(const double* uvw, int64_t nvis, int n, double cell, int os, int nplanes,
-                            const double* w_planes, const PlaneInfo* planes, int nt, uint64_t drop_key,
-                            uint64_t* keys, int32_t* vals, int2* fine_all, hipStream_t s);
-hipError_t radix_sort_pairs(uint64_t* keys, int32_t* vals, uint64_t* keys_tmp, int32_t* vals_tmp,
-                            int64_t n, int bits, int32_t* scratch, int64_t scratch_elems, hipStream_t s,
-                            bool* result_in_tmp);
-int64_t radix_scratch_elems(int64_t n);
-int64_t plan_scratch_elems(int64_t nvis);
-hipError_t launch_plan_stage_a(const uint64_t* keys_sorted, int64_t nvis, uint64_t drop_key, int os,
-                               int max_chunk, int32_t* counts, int32_t* scratch, int64_t scratch_elems,
-                               hipStream_t s);
-hipError_t launch_plan_scatter(const uint64_t* keys_sorted, const int32_t* perm, const int2* fine_all,
-                               int64_t n_kept, int64_t n_runs, int64_t nvis, int os, int nt, int max_chunk,
-                               const PlaneInfo* planes, const int32_t* scratch, int2* fine_sorted, Item* items,
-                               hipStream_t s);
+struct PlanSort {
+  const double* uvw;
+  int64_t nvis;
+  int n;
+  double cell;
+  int os, nplanes;
+  const double* w_planes;
+  const PlaneInfo* planes;
+  int nt, max_chunk;
+  int bits;            // of the binning keys, drop_key = 2^bits - 1 among them
+  uint64_t drop_key;
+  void* scratch;       // plan_scratch_bytes(nvis, bits)
+};
+size_t plan_scratch_bytes(int64_t nvis, int bits);
+// The permutation into binned order; *counts (device): rows kept, work items.
+hipError_t launch_plan_sort(const PlanSort& a, int32_t* perm, const int32_t** counts, hipStream_t s);
+// Fine positions and work items, from the same scratch.
+hipError_t launch_plan_items(const PlanSort& a, int64_t n_kept, int64_t n_items, const int32_t* perm, int2* fine,
+                             Item* items, hipStream_t s);
 
 // Gridding (grid.hip)
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);

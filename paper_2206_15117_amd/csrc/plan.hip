@@ -3,363 +3,526 @@
 //
 // The snapping arithmetic is written with floating-point contraction off so the
 // fine-grid integers are the ones plain float64 multiply/add produces.
-#include <climits>
-
+//
+// Launch and synchronisation latency bound it at small sizes, the scattered 8-byte writes of a sort
+// pass and the gather of the fine positions at large ones.  2.3M rows (25-bit keys, three passes):
+// 14 launches, 280 us with the caller's allocations; with 8-bit digits on 64-bit keys and scans of
+// several launches each it was 37 launches and 405 us.
 #include "common.hpp"
 
 namespace pg {
 namespace {
 
-__device__ inline int64_t ceil_div_pos(int64_t a, int64_t b) {  // b > 0
-  return a >= 0 ? (a + b - 1) / b : -((-a) / b);
+__device__ inline int ceil_div_i(int a, int b) { return a >= 0 ? (a + b - 1) / b : -((-a) / b); }
+
+// ---------------------------------------------------------------- stable LSD radix sort
+// Digits of up to 9 bits (the fewest passes that cover the key, bits spread evenly).  A pass is three
+// launches: digit counts per workgroup (the first pass's come with the keys), an exclusive scan of
+// each digit's row of counts, and the scatter.  A workgroup of 16 waves takes a tile of 4096 elements,
+// each wave 256 consecutive ones in four rounds of 64.  The rounds are a serial chain: with 16 (tiles
+// of 16384, which write whole cache lines of a digit) 2.3M rows took 309 us and 20M 1556 us, with 8
+// 315 and 1453, with 4 280 and 1443.
+constexpr int kSortThreads = 1024, kSortWaves = kSortThreads / 64, kSortRounds = 4;
+constexpr int kSortTile = kSortThreads * kSortRounds, kDigitBits = 9, kDigits = 1 << kDigitBits;
+constexpr int64_t tiles_of(int64_t n) { return (n + kSortTile - 1) / kSortTile; }
+
+__device__ __forceinline__ int64_t sort_index(int round) {  // element of this thread in round `round`
+  return static_cast<int64_t>(blockIdx.x) * kSortTile + (threadIdx.x >> 6) * (64 * kSortRounds) + round * 64 +
+         (threadIdx.x & 63);
 }
 
-__global__ void plan_keys_kernel(const double* __restrict__ uvw, int64_t nvis, int n, double ncell,
-                                 double half_n, int os, int nplanes, const double* __restrict__ w_planes,
-                                 const PlaneInfo* __restrict__ planes, int nt, uint64_t drop_key,
-                                 uint64_t* __restrict__ keys, int32_t* __restrict__ vals,
-                                 int2* __restrict__ fine_all) {
+template <typename KeyT>
+__device__ __forceinline__ int digit_of(KeyT key, int shift, int bits) {
+  return static_cast<int>(key >> shift) & ((1 << bits) - 1);
+}
+
+// Nearest plane of the ascending w_planes, the lowest index among equal distances, as a scan from plane
+// 0 that keeps strictly smaller distances finds it: the rounded distances fall towards the planes
+// around w and rise behind them, so it is one of those two or a lower one at the same distance.
+__device__ __forceinline__ int nearest_plane(double w, const double* w_planes, int nplanes) {
 #pragma clang fp contract(off)
-  const int64_t k = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (k >= nvis) return;
-  const double u = uvw[3 * k], v = uvw[3 * k + 1], w = uvw[3 * k + 2];
-  const double x = u * ncell + half_n;
-  const double y = v * ncell + half_n;
-  const double fxd = floor(x * static_cast<double>(os) + 0.5);
-  const double fyd = floor(y * static_cast<double>(os) + 0.5);
-  uint64_t key = drop_key;
-  int2 f = make_int2(0, 0);
-  if (isfinite(fxd) && isfinite(fyd) && isfinite(w) && fabs(fxd) < 1e9 && fabs(fyd) < 1e9) {
-    const int64_t fx = static_cast<int64_t>(fxd), fy = static_cast<int64_t>(fyd);
-    int p = 0;
-    double best = fabs(w - w_planes[0]);
-    for (int q = 1; q < nplanes; ++q) {
-      double d = fabs(w - w_planes[q]);
-      if (d < best) {
-        best = d;
-        p = q;
+  int lo = 0, hi = nplanes;  // planes below lo are <= w, planes from hi on are > w
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (w_planes[mid] <= w)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  int p = lo > 0 ? lo - 1 : 0;
+  double best = fabs(w - w_planes[p]);
+  if (lo > 0 && lo < nplanes) {
+    const double d = fabs(w - w_planes[lo]);
+    if (d < best) {
+      best = d;
+      p = lo;
+    }
+  }
+  while (p > 0 && fabs(w - w_planes[p - 1]) <= best) --p;
+  return p;
+}
+
+template <typename KeyT>
+__global__ __launch_bounds__(kSortThreads) void plan_keys_kernel(const double* __restrict__ uvw, int64_t nvis, int n,
+                                                                 double ncell, double half_n, int os, int nplanes,
+                                                                 const double* __restrict__ w_planes,
+                                                                 const PlaneInfo* __restrict__ planes, int nt,
+                                                                 KeyT drop_key, KeyT* __restrict__ keys,
+                                                                 int2* __restrict__ fine_all, int digit_bits,
+                                                                 int32_t* __restrict__ hist, int32_t* __restrict__ counts) {
+#pragma clang fp contract(off)
+  __shared__ int32_t h[kDigits];
+  extern __shared__ double plane_w[];  // [nplanes] centres, then [nplanes] (support, tile)
+  int2* plane_st = reinterpret_cast<int2*>(plane_w + nplanes);
+  for (int p = threadIdx.x; p < nplanes; p += kSortThreads) {
+    plane_w[p] = w_planes[p];
+    plane_st[p] = make_int2(planes[p].support, planes[p].tile);
+  }
+  for (int d = threadIdx.x; d < kDigits; d += kSortThreads) h[d] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 4) counts[threadIdx.x] = 0;
+  __syncthreads();
+  double c[kSortRounds][3];  // the rounds' coordinates are requested together
+#pragma unroll
+  for (int r = 0; r < kSortRounds; ++r) {
+    const int64_t k = min(sort_index(r), nvis - 1);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) c[r][i] = uvw[3 * k + i];
+  }
+#pragma unroll
+  for (int r = 0; r < kSortRounds; ++r) {
+    const int64_t k = sort_index(r);
+    if (k >= nvis) continue;
+    const double u = c[r][0], v = c[r][1], w = c[r][2];
+    const double x = u * ncell + half_n;
+    const double y = v * ncell + half_n;
+    const double fxd = floor(x * static_cast<double>(os) + 0.5);
+    const double fyd = floor(y * static_cast<double>(os) + 0.5);
+    KeyT key = drop_key;
+    int2 f = make_int2(0, 0);
+    if (isfinite(fxd) && isfinite(fyd) && isfinite(w) && fabs(fxd) < 1e9 && fabs(fyd) < 1e9) {
+      const int fx = static_cast<int>(fxd), fy = static_cast<int>(fyd);
+      const int p = nearest_plane(w, plane_w, nplanes);
+      const int2 st = plane_st[p];
+      const int S = st.x, half = S * os / 2;
+      const int x0 = ceil_div_i(fx - half + 1, os), y0 = ceil_div_i(fy - half + 1, os);
+      const int phx = x0 * os - fx + half - 1, phy = y0 * os - fy + half - 1;
+      if (x0 >= 0 && y0 >= 0 && x0 + S <= n && y0 + S <= n) {
+        const KeyT ty = static_cast<KeyT>(y0 / st.y), tx = static_cast<KeyT>(x0 / st.y);
+        key = (((static_cast<KeyT>(p) * nt + ty) * nt + tx) * os + static_cast<KeyT>(phy)) * os + static_cast<KeyT>(phx);
+        f = make_int2(fx, fy);
       }
     }
-    const PlaneInfo pi = planes[p];
-    const int64_t S = pi.support, half = S * os / 2;
-    const int64_t x0 = ceil_div_pos(fx - half + 1, os), y0 = ceil_div_pos(fy - half + 1, os);
-    const int64_t phx = x0 * os - fx + half - 1, phy = y0 * os - fy + half - 1;
-    if (x0 >= 0 && y0 >= 0 && x0 + S <= n && y0 + S <= n) {
-      const uint64_t ty = static_cast<uint64_t>(y0 / pi.tile), tx = static_cast<uint64_t>(x0 / pi.tile);
-      key = (((static_cast<uint64_t>(p) * nt + ty) * nt + tx) * os + static_cast<uint64_t>(phy)) * os +
-            static_cast<uint64_t>(phx);
-      f = make_int2(static_cast<int>(fx), static_cast<int>(fy));
+    keys[k] = key;
+    fine_all[k] = f;
+    atomicAdd(&h[digit_of(key, 0, digit_bits)], 1);
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < (1 << digit_bits); d += kSortThreads)
+    hist[static_cast<int64_t>(d) * gridDim.x + blockIdx.x] = h[d];
+}
+
+template <typename KeyT>
+__global__ __launch_bounds__(kSortThreads) void radix_count(const KeyT* __restrict__ keys, int64_t n, int shift,
+                                                            int digit_bits, int32_t* __restrict__ hist) {
+  __shared__ int32_t h[kDigits];
+  for (int d = threadIdx.x; d < kDigits; d += kSortThreads) h[d] = 0;
+  __syncthreads();
+#pragma unroll 4
+  for (int r = 0; r < kSortRounds; ++r) {
+    const int64_t k = sort_index(r);
+    if (k < n) atomicAdd(&h[digit_of(keys[k], shift, digit_bits)], 1);
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < (1 << digit_bits); d += kSortThreads)
+    hist[static_cast<int64_t>(d) * gridDim.x + blockIdx.x] = h[d];
+}
+
+// Exclusive sums over a workgroup of T threads (one value each), and their total.
+template <int T>
+__device__ __forceinline__ int32_t workgroup_exclusive(int32_t v, int32_t* sh, int32_t* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int32_t s = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t t = __shfl_up(s, o, 64);
+    if (lane >= o) s += t;
+  }
+  if (lane == 63) sh[wave] = s;
+  __syncthreads();
+  int32_t before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < T / 64; ++w) {
+    if (w < wave) before += sh[w];
+    all += sh[w];
+  }
+  __syncthreads();
+  *total = all;
+  return before + s - v;
+}
+
+// Workgroup d: the counts of digit d over the tiles become their exclusive sums, in place; total[d].
+constexpr int kRowThreads = 256;
+__global__ __launch_bounds__(kRowThreads) void radix_rows(int32_t* __restrict__ hist, int64_t tiles,
+                                                           int32_t* __restrict__ total) {
+  __shared__ int32_t sh[kRowThreads / 64];
+  int32_t* row = hist + static_cast<int64_t>(blockIdx.x) * tiles;
+  int32_t carry = 0;
+  for (int64_t t0 = 0; t0 < tiles; t0 += 4 * kRowThreads) {
+    const int64_t t = t0 + 4 * threadIdx.x;
+    int32_t v[4], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = t + i < tiles ? row[t + i] : 0;
+      sum += v[i];
     }
-  }
-  keys[k] = key;
-  vals[k] = static_cast<int32_t>(k);
-  fine_all[k] = f;
-}
-
-// ---------------------------------------------------------------- scans (int32, exclusive or inclusive)
-constexpr int SCAN_THREADS = 256, SCAN_ITEMS = 8, SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
-
-struct OpSum {
-  __device__ static int32_t id() { return 0; }
-  __device__ static int32_t op(int32_t a, int32_t b) { return a + b; }
-};
-
-template <class Op>
-__device__ int32_t block_exclusive(int32_t v, int32_t* sh, int32_t* total) {
-  const int tid = threadIdx.x;
-  sh[tid] = v;
-  __syncthreads();
-  for (int off = 1; off < SCAN_THREADS; off <<= 1) {
-    int32_t t = tid >= off ? sh[tid - off] : Op::id();
-    __syncthreads();
-    sh[tid] = Op::op(sh[tid], t);
-    __syncthreads();
-  }
-  int32_t incl = sh[tid];
-  *total = sh[SCAN_THREADS - 1];
-  int32_t excl = tid ? sh[tid - 1] : Op::id();
-  __syncthreads();
-  (void)incl;
-  return excl;
-}
-
-template <class Op>
-__global__ void tile_reduce(const int32_t* __restrict__ in, int64_t n, int32_t* __restrict__ part) {
-  __shared__ int32_t sh[SCAN_THREADS];
-  const int64_t base = static_cast<int64_t>(blockIdx.x) * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-  int32_t acc = Op::id();
-  for (int i = 0; i < SCAN_ITEMS; ++i)
-    if (base + i < n) acc = Op::op(acc, in[base + i]);
-  int32_t total;
-  block_exclusive<Op>(acc, sh, &total);
-  if (threadIdx.x == 0) part[blockIdx.x] = total;
-}
-
-template <class Op>
-__global__ void tile_scan(const int32_t* in, int32_t* out, int64_t n, const int32_t* part_excl,
-                          bool inclusive) {  // in may equal out: each thread reads its items before writing
-  __shared__ int32_t sh[SCAN_THREADS];
-  const int64_t base = static_cast<int64_t>(blockIdx.x) * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-  int32_t v[SCAN_ITEMS];
-  int32_t acc = Op::id();
-  for (int i = 0; i < SCAN_ITEMS; ++i) {
-    v[i] = base + i < n ? in[base + i] : Op::id();
-    acc = Op::op(acc, v[i]);
-  }
-  int32_t total;
-  int32_t run = block_exclusive<Op>(acc, sh, &total);
-  if (part_excl) run = Op::op(part_excl[blockIdx.x], run);
-  for (int i = 0; i < SCAN_ITEMS; ++i) {
-    int32_t nxt = Op::op(run, v[i]);
-    if (base + i < n) out[base + i] = inclusive ? nxt : run;
-    run = nxt;
-  }
-}
-
-template <class Op>
-hipError_t scan(const int32_t* in, int32_t* out, int64_t n, bool inclusive, int32_t* scratch, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  const int64_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
-  if (tiles == 1) {
-    hipLaunchKernelGGL(tile_scan<Op>, dim3(1), dim3(SCAN_THREADS), 0, s, in, out, n, nullptr, inclusive);
-    return hipGetLastError();
-  }
-  int32_t* part = scratch;
-  hipLaunchKernelGGL(tile_reduce<Op>, dim3(tiles), dim3(SCAN_THREADS), 0, s, in, n, part);
-  hipError_t e = scan<Op>(part, part, tiles, false, scratch + tiles, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(tile_scan<Op>, dim3(tiles), dim3(SCAN_THREADS), 0, s, in, out, n, part, inclusive);
-  return hipGetLastError();
-}
-
-int64_t scan_scratch(int64_t n) {
-  int64_t total = 0;
-  while (n > SCAN_TILE) {
-    n = (n + SCAN_TILE - 1) / SCAN_TILE;
-    total += n;
-  }
-  return total + 16;
-}
-
-// ---------------------------------------------------------------- stable LSD radix sort, 8-bit digits
-constexpr int RS_THREADS = 256, RS_ROUNDS = 16, RS_TILE = RS_THREADS * RS_ROUNDS;
-
-__global__ __launch_bounds__(RS_THREADS) void radix_hist(const uint64_t* __restrict__ keys, int64_t n, int shift,
-                                                         int32_t* __restrict__ hist, int nblocks) {
-  __shared__ int32_t h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t base = static_cast<int64_t>(blockIdx.x) * RS_TILE;
-  for (int i = threadIdx.x; i < RS_TILE; i += RS_THREADS) {
-    int64_t g = base + i;
-    if (g < n) atomicAdd(&h[(keys[g] >> shift) & 255], 1);
-  }
-  __syncthreads();
-  hist[threadIdx.x * static_cast<int64_t>(nblocks) + blockIdx.x] = h[threadIdx.x];
-}
-
-// Each block writes its tile in index order: the rank of an element is the global offset of its
-// digit for this block, plus the elements of the same digit earlier in the tile (earlier rounds,
-// earlier waves of this round, lower lanes of this wave).
-__global__ __launch_bounds__(RS_THREADS) void radix_scatter(const uint64_t* __restrict__ kin,
-                                                            const int32_t* __restrict__ vin,
-                                                            uint64_t* __restrict__ kout, int32_t* __restrict__ vout,
-                                                            int64_t n, int shift, const int32_t* __restrict__ offs,
-                                                            int nblocks) {
-  __shared__ int32_t run[256];
-  __shared__ int32_t wcnt[4][256];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  run[tid] = offs[tid * static_cast<int64_t>(nblocks) + blockIdx.x];
-  const int64_t base = static_cast<int64_t>(blockIdx.x) * RS_TILE;
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int r = 0; r < RS_ROUNDS; ++r) {
-    wcnt[0][tid] = 0;
-    wcnt[1][tid] = 0;
-    wcnt[2][tid] = 0;
-    wcnt[3][tid] = 0;
-    __syncthreads();
-    const int64_t g = base + r * RS_THREADS + tid;
-    const bool valid = g < n;
-    const uint64_t key = valid ? kin[g] : 0;
-    const int32_t val = valid ? vin[g] : 0;
-    const int digit = valid ? static_cast<int>((key >> shift) & 255) : 256;
-    uint64_t m = ~0ull;
-    for (int b = 0; b < 9; ++b) {
-      const int bit = (digit >> b) & 1;
-      const uint64_t bal = __ballot(bit);
-      m &= bit ? bal : ~bal;
+    int32_t all;
+    int32_t run = carry + workgroup_exclusive<kRowThreads>(sum, sh, &all);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (t + i < tiles) row[t + i] = run;
+      run += v[i];
     }
-    const int rank = __popcll(m & lt);
-    if (valid && rank == 0) wcnt[wave][digit] = __popcll(m);
-    __syncthreads();
+    carry += all;
+  }
+  if (threadIdx.x == 0) total[blockIdx.x] = carry;
+}
+
+// The rank of an element inside its digit is the count of the lower digits, plus that of the digit in
+// earlier tiles, earlier waves of this tile, and earlier rounds and lower lanes of its wave.  Each wave
+// counts for itself, round after round (its LDS operations execute in program order), so the tile
+// needs two barriers: 16 rounds that counted across the four waves with three barriers each took
+// 27.6 us a pass at 2.3M elements.
+template <typename KeyT, bool FIRST>
+__global__ __launch_bounds__(kSortThreads) void radix_scatter(const KeyT* __restrict__ kin,
+                                                              const int32_t* __restrict__ vin, KeyT* __restrict__ kout,
+                                                              int32_t* __restrict__ vout, int64_t n, int shift,
+                                                              int digit_bits, const int32_t* __restrict__ offs,
+                                                              const int32_t* __restrict__ total) {
+  __shared__ int32_t cnt[kSortWaves][kDigits];
+  __shared__ int32_t sh[kSortWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, digits = 1 << digit_bits;
+  for (int d = threadIdx.x; d < kSortWaves * kDigits; d += kSortThreads) (&cnt[0][0])[d] = 0;
+  KeyT key[kSortRounds];
+  int32_t val[kSortRounds], rank[kSortRounds];
+#pragma unroll
+  for (int r = 0; r < kSortRounds; ++r) {
+    const int64_t k = sort_index(r);
+    key[r] = k < n ? kin[k] : KeyT(0);
+    val[r] = k < n ? (FIRST ? static_cast<int32_t>(k) : vin[k]) : 0;
+  }
+  __syncthreads();
+  volatile int32_t* mine = cnt[wave];
+  const uint64_t below = (1ull << lane) - 1;
+#pragma unroll
+  for (int r = 0; r < kSortRounds; ++r) {
+    const bool valid = sort_index(r) < n;
+    const int d = digit_of(key[r], shift, digit_bits);
+    uint64_t same = __ballot(valid);
+    for (int b = 0; b < digit_bits; ++b) {
+      const uint64_t set = __ballot((d >> b) & 1);
+      same &= ((d >> b) & 1) ? set : ~set;
+    }
     if (valid) {
-      int pos = run[digit] + rank;
-      for (int w2 = 0; w2 < wave; ++w2) pos += wcnt[w2][digit];
-      kout[pos] = key;
-      vout[pos] = val;
+      const int32_t old = mine[d];
+      rank[r] = old + __popcll(same & below);
+      __builtin_amdgcn_wave_barrier();
+      if ((same & below) == 0) mine[d] = old + __popcll(same);
     }
-    __syncthreads();
-    run[tid] += wcnt[0][tid] + wcnt[1][tid] + wcnt[2][tid] + wcnt[3][tid];
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  // digit base: lower digits, earlier tiles, then the waves in turn
+  const int d = threadIdx.x;
+  int32_t all;
+  const int32_t base = workgroup_exclusive<kSortThreads>(d < digits ? total[d] : 0, sh, &all);
+  if (d < digits) {
+    int32_t at = base + offs[static_cast<int64_t>(d) * gridDim.x + blockIdx.x];
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) {
+      const int32_t c = cnt[w][d];
+      cnt[w][d] = at;
+      at += c;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kSortRounds; ++r) {
+    if (sort_index(r) < n) {
+      const int32_t pos = cnt[wave][digit_of(key[r], shift, digit_bits)] + rank[r];
+      kout[pos] = key[r];
+      vout[pos] = val[r];
+    }
   }
 }
 
 // ---------------------------------------------------------------- work items
-// Runs of one (plane, tile) bin are compacted with exclusive sum-scans only:
-//   run flags -> run index -> run start positions -> chunks per run -> item offsets.
-__global__ void count_kept(const uint64_t* __restrict__ keys, int64_t n, uint64_t drop_key, int32_t* counts) {
-  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (i >= n) return;
-  if (keys[i] != drop_key && (i + 1 == n || keys[i + 1] == drop_key)) counts[0] = static_cast<int32_t>(i + 1);
-}
+// Division by a value that is the same for the whole launch, a shift where it is a power of two.
+struct Divisor {
+  uint32_t by;
+  int shift;  // -1: not a power of two
+  explicit Divisor(uint32_t d) : by(d), shift((d & (d - 1)) == 0 ? __builtin_ctz(d) : -1) {}
+  template <typename T>
+  __device__ __forceinline__ T quotient(T v) const { return shift >= 0 ? v >> shift : v / by; }
+  __device__ __forceinline__ bool divides(uint32_t v) const { return shift >= 0 ? (v & (by - 1)) == 0 : v % by == 0; }
+};
 
-__global__ void run_flags(const uint64_t* __restrict__ keys, int64_t n, const int32_t* counts, int os,
-                          int32_t* __restrict__ flag) {
-  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (i >= n) return;
-  const int64_t nk = counts[0];
-  const uint64_t oo = static_cast<uint64_t>(os) * os;
-  flag[i] = (i < nk && (i == 0 || keys[i] / oo != keys[i - 1] / oo)) ? 1 : 0;
-}
-
-__global__ void run_scatter(const int32_t* __restrict__ flag, const int32_t* __restrict__ ridx, int64_t n,
-                            int32_t* __restrict__ rstart, int32_t* counts) {
-  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (i >= n) return;
-  if (flag[i]) rstart[ridx[i]] = static_cast<int32_t>(i);
-  if (i == n - 1) counts[2] = ridx[i] + flag[i];  // number of runs
-}
-
-__global__ void run_chunks(const int32_t* __restrict__ rstart, int64_t n, const int32_t* counts, int max_chunk,
-                           int32_t* __restrict__ nchunk) {
-  const int64_t r = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (r >= n) return;
-  const int64_t nruns = counts[2], nk = counts[0];
-  int32_t c = 0;
-  if (r < nruns) {
-    const int64_t len = (r + 1 < nruns ? rstart[r + 1] : nk) - rstart[r];
-    c = static_cast<int32_t>((len + max_chunk - 1) / max_chunk);
+// An item starts where a (plane, tile) run of the sorted keys starts, or a multiple of max_chunk rows
+// behind that.  Tiles of the sorted keys as in the sort, kSortRounds consecutive ones per thread here; a first
+// pass leaves each tile's last run start, a second counts its items (with the run start it inherits),
+// a third writes them.  An item ends where the next one starts.
+template <typename KeyT>
+struct RunTile {
+  KeyT key[kSortRounds];
+  int64_t first;  // position of key[0]
+  // run starts among this thread's positions; `last`: the largest (-1: none)
+  __device__ __forceinline__ uint32_t load(const KeyT* __restrict__ keys, int64_t n, KeyT drop_key, Divisor os2,
+                                           int64_t* last) {
+    first = (static_cast<int64_t>(blockIdx.x) * kSortThreads + threadIdx.x) * kSortRounds;
+#pragma unroll
+    for (int i = 0; i < kSortRounds; ++i) key[i] = first + i < n ? keys[first + i] : drop_key;
+    KeyT bin = first > 0 && first <= n ? os2.quotient(keys[first - 1]) : KeyT(0);
+    uint32_t starts = 0;
+    *last = -1;
+#pragma unroll
+    for (int i = 0; i < kSortRounds; ++i) {
+      const KeyT b = os2.quotient(key[i]);
+      if (key[i] != drop_key && (first + i == 0 || b != bin)) {
+        starts |= 1u << i;
+        *last = first + i;
+      }
+      bin = b;
+    }
+    return starts;
   }
-  nchunk[r] = c;
+};
+
+// Largest value over the threads before this one in the workgroup (-1: none), and over all of them.
+__device__ __forceinline__ int64_t workgroup_max_before(int64_t v, int64_t* sh, int64_t* all) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int64_t s = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int64_t t = __shfl_up(s, o, 64);
+    if (lane >= o && t > s) s = t;
+  }
+  if (lane == 63) sh[wave] = s;
+  int64_t m = __shfl_up(s, 1, 64);
+  if (lane == 0) m = -1;
+  __syncthreads();
+  int64_t top = -1;
+#pragma unroll
+  for (int w = 0; w < kSortWaves; ++w) {
+    if (w < wave && sh[w] > m) m = sh[w];
+    if (sh[w] > top) top = sh[w];
+  }
+  __syncthreads();
+  *all = top;
+  return m;
 }
 
-__global__ void item_total(const int32_t* __restrict__ nchunk, const int32_t* __restrict__ cidx, int64_t n,
-                           int32_t* counts) {
-  counts[1] = cidx[n - 1] + nchunk[n - 1];
+template <typename KeyT>
+__global__ __launch_bounds__(kSortThreads) void run_ends(const KeyT* __restrict__ keys, int64_t n, KeyT drop_key,
+                                                         Divisor os2, int64_t* __restrict__ last_start,
+                                                         int32_t* __restrict__ counts) {
+  __shared__ int64_t sh[kSortWaves];
+  RunTile<KeyT> t;
+  int64_t last, top;
+  t.load(keys, n, drop_key, os2, &last);
+  workgroup_max_before(last, sh, &top);
+  if (threadIdx.x == 0) last_start[blockIdx.x] = top;
+#pragma unroll
+  for (int i = 0; i < kSortRounds; ++i) {
+    const int64_t k = t.first + i;
+    if (k < n && t.key[i] != drop_key) {
+      const KeyT next = i + 1 < kSortRounds ? t.key[(i + 1) % kSortRounds] : (k + 1 < n ? keys[k + 1] : drop_key);
+      if (k + 1 == n || next == drop_key) counts[0] = static_cast<int32_t>(k + 1);  // rows kept
+    }
+  }
 }
 
-__global__ void fine_gather(const int32_t* __restrict__ perm, const int2* __restrict__ fine_all, int64_t n_kept,
-                            int2* __restrict__ fine_sorted) {
+// Item starts among this thread's positions.
+template <typename KeyT>
+__device__ __forceinline__ uint32_t item_starts(RunTile<KeyT>& t, const KeyT* __restrict__ keys, int64_t n,
+                                                KeyT drop_key, Divisor os2, Divisor max_chunk,
+                                                const int64_t* __restrict__ last_start, int64_t* sh) {
+  int64_t last, top;
+  const uint32_t starts = t.load(keys, n, drop_key, os2, &last);
+  int64_t run = workgroup_max_before(last, sh, &top);
+  // the run that reaches into this tile starts in the nearest tile before it that has a start
+  __shared__ int64_t inherited;
+  if (threadIdx.x < 64) {
+    int64_t found = -1;
+    for (int64_t b = static_cast<int64_t>(blockIdx.x) - 64; found < 0 && b > -64; b -= 64) {
+      int64_t v = b + threadIdx.x >= 0 ? last_start[b + threadIdx.x] : -1;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const int64_t other = __shfl_xor(v, o, 64);
+        v = other > v ? other : v;
+      }
+      found = v;
+    }
+    if (threadIdx.x == 0) inherited = found;
+  }
+  __syncthreads();
+  if (run < 0) run = inherited;
+  uint32_t items = 0;
+#pragma unroll
+  for (int i = 0; i < kSortRounds; ++i) {
+    if (starts >> i & 1) run = t.first + i;
+    if (t.key[i] != drop_key &&
+        max_chunk.divides(static_cast<uint32_t>(t.first + i - run)))
+      items |= 1u << i;
+  }
+  return items;
+}
+
+template <typename KeyT>
+__global__ __launch_bounds__(kSortThreads) void item_count(const KeyT* __restrict__ keys, int64_t n, KeyT drop_key,
+                                                           Divisor os2, Divisor max_chunk,
+                                                           const int64_t* __restrict__ last_start,
+                                                           int32_t* __restrict__ tile_items) {
+  __shared__ int64_t sh[kSortWaves];
+  __shared__ int32_t sum[kSortWaves];
+  RunTile<KeyT> t;
+  int32_t all;
+  workgroup_exclusive<kSortThreads>(__popc(item_starts(t, keys, n, drop_key, os2, max_chunk, last_start, sh)), sum, &all);
+  if (threadIdx.x == 0) tile_items[blockIdx.x] = all;
+}
+
+template <typename KeyT>
+__global__ __launch_bounds__(kSortThreads) void item_write(const KeyT* __restrict__ keys, int64_t n, KeyT drop_key,
+                                                           Divisor os2, Divisor max_chunk,
+                                                           const int64_t* __restrict__ last_start,
+                                                           const int32_t* __restrict__ tile_items, int nt,
+                                                           const PlaneInfo* __restrict__ planes,
+                                                           Item* __restrict__ items) {
+  __shared__ int64_t sh[kSortWaves];
+  __shared__ int32_t sum[kSortWaves];
+  RunTile<KeyT> t;
+  const uint32_t mask = item_starts(t, keys, n, drop_key, os2, max_chunk, last_start, sh);
+  int32_t all;
+  int32_t at = tile_items[blockIdx.x] + workgroup_exclusive<kSortThreads>(__popc(mask), sum, &all);
+  const KeyT nt2 = static_cast<KeyT>(nt) * nt;
+#pragma unroll
+  for (int i = 0; i < kSortRounds; ++i) {
+    if (!(mask >> i & 1)) continue;
+    const KeyT bin = os2.quotient(t.key[i]), rest = bin % nt2;
+    Item it;
+    it.plane = static_cast<int>(bin / nt2);
+    const int tile = planes[it.plane].tile;
+    it.oy = static_cast<int32_t>(rest / nt) * tile;
+    it.ox = static_cast<int32_t>(rest % nt) * tile;
+    it.start = static_cast<int32_t>(t.first + i);
+    it.end = 0;
+    it.pad[0] = it.pad[1] = it.pad[2] = 0;
+    items[at++] = it;
+  }
+}
+
+// Fine positions in binned order, and the items' ends.
+__global__ void plan_finish(const int32_t* __restrict__ perm, const int2* __restrict__ fine_all, int64_t n_kept,
+                            int2* __restrict__ fine_sorted, int64_t n_items, Item* __restrict__ items) {
   const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
   if (i < n_kept) fine_sorted[i] = fine_all[perm[i]];
+  if (i < n_items) items[i].end = i + 1 < n_items ? items[i + 1].start : static_cast<int32_t>(n_kept);
 }
 
-__global__ void item_write(const uint64_t* __restrict__ keys, const int32_t* __restrict__ rstart,
-                           const int32_t* __restrict__ nchunk, const int32_t* __restrict__ cidx, int64_t n_runs,
-                           int64_t n_kept, int os, int nt, int max_chunk, const PlaneInfo* __restrict__ planes,
-                           Item* __restrict__ items) {
-  const int64_t r = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (r >= n_runs) return;
-  const int64_t s0 = rstart[r];
-  const int64_t e0 = (r + 1 < n_runs) ? rstart[r + 1] : n_kept;
-  const uint64_t bin = keys[s0] / (static_cast<uint64_t>(os) * os);
-  const uint64_t nt2 = static_cast<uint64_t>(nt) * nt;
-  const int plane = static_cast<int>(bin / nt2);
-  const uint64_t rest = bin % nt2;
-  const int tile = planes[plane].tile;
-  Item it;
-  it.plane = plane;
-  it.oy = static_cast<int32_t>(rest / nt) * tile;
-  it.ox = static_cast<int32_t>(rest % nt) * tile;
-  it.pad[0] = it.pad[1] = it.pad[2] = 0;
-  for (int32_t c = 0; c < nchunk[r]; ++c) {
-    const int64_t a = s0 + static_cast<int64_t>(c) * max_chunk;
-    it.start = static_cast<int32_t>(a);
-    it.end = static_cast<int32_t>(a + max_chunk < e0 ? a + max_chunk : e0);
-    items[cidx[r] + c] = it;
+template <typename T>
+T* take(char*& at, int64_t count) {  // the next part of the scratch, 256-byte aligned
+  T* p = reinterpret_cast<T*>(at);
+  at += (static_cast<size_t>(count) * sizeof(T) + 255) / 256 * 256;
+  return p;
+}
+
+struct Scratch {
+  void *key[2];
+  int32_t *val, *hist, *total, *tile_items, *counts;
+  int64_t* last_start;
+  int2* fine_all;
+  size_t bytes;
+};
+
+Scratch scratch_at(char* base, int64_t nvis, int key_bytes) {
+  const int64_t tiles = tiles_of(nvis);
+  char* at = base;
+  Scratch s;
+  for (auto& k : s.key) k = take<char>(at, nvis * key_bytes);
+  s.val = take<int32_t>(at, nvis);
+  s.fine_all = take<int2>(at, nvis);
+  s.hist = take<int32_t>(at, tiles * kDigits);
+  s.total = take<int32_t>(at, kDigits);
+  s.tile_items = take<int32_t>(at, tiles);
+  s.last_start = take<int64_t>(at, tiles);
+  s.counts = take<int32_t>(at, 4);
+  s.bytes = static_cast<size_t>(at - base);
+  return s;
+}
+
+int key_bytes_of(int bits) { return bits <= 32 ? 4 : 8; }
+int passes_of(int bits) { return (bits + kDigitBits - 1) / kDigitBits; }
+
+template <typename KeyT>
+hipError_t run_sort(const PlanSort& a, int32_t* perm, hipStream_t s) {
+  const Scratch b = scratch_at(static_cast<char*>(a.scratch), a.nvis, sizeof(KeyT));
+  const dim3 tiles(static_cast<unsigned>(tiles_of(a.nvis))), threads(kSortThreads);
+  const KeyT drop = static_cast<KeyT>(a.drop_key);
+  const int passes = passes_of(a.bits);
+  const auto digit_bits = [&](int p) { return a.bits / passes + (p < a.bits % passes ? 1 : 0); };
+  KeyT* key[2] = {static_cast<KeyT*>(b.key[0]), static_cast<KeyT*>(b.key[1])};
+  hipLaunchKernelGGL(plan_keys_kernel<KeyT>, tiles, threads, 16 * static_cast<size_t>(a.nplanes), s, a.uvw, a.nvis, a.n, static_cast<double>(a.n) * a.cell,
+                     a.n / 2.0, a.os, a.nplanes, a.w_planes, a.planes, a.nt, drop, key[0], b.fine_all, digit_bits(0), b.hist,
+                     b.counts);
+  for (int p = 0, shift = 0; p < passes; ++p) {
+    const int db = digit_bits(p);
+    if (p > 0) hipLaunchKernelGGL(radix_count<KeyT>, tiles, threads, 0, s, key[p & 1], a.nvis, shift, db, b.hist);
+    hipLaunchKernelGGL(radix_rows, dim3(1u << db), dim3(kRowThreads), 0, s, b.hist, static_cast<int64_t>(tiles.x), b.total);
+    // the values alternate so that the last pass writes the permutation itself
+    int32_t* out = (passes - 1 - p) % 2 == 0 ? perm : b.val;
+    const int32_t* in = out == perm ? b.val : perm;
+    if (p == 0)
+      hipLaunchKernelGGL((radix_scatter<KeyT, true>), tiles, threads, 0, s, key[0], in, key[1], out, a.nvis, shift, db,
+                         b.hist, b.total);
+    else
+      hipLaunchKernelGGL((radix_scatter<KeyT, false>), tiles, threads, 0, s, key[p & 1], in, key[(p + 1) & 1], out, a.nvis,
+                         shift, db, b.hist, b.total);
+    shift += db;
   }
+  const KeyT* sorted = key[passes & 1];
+  const Divisor os2(static_cast<uint32_t>(a.os) * a.os), chunk(static_cast<uint32_t>(a.max_chunk));
+  hipLaunchKernelGGL(run_ends<KeyT>, tiles, threads, 0, s, sorted, a.nvis, drop, os2, b.last_start, b.counts);
+  hipLaunchKernelGGL(item_count<KeyT>, tiles, threads, 0, s, sorted, a.nvis, drop, os2, chunk, b.last_start,
+                     b.tile_items);
+  hipLaunchKernelGGL(radix_rows, dim3(1), dim3(kRowThreads), 0, s, b.tile_items, static_cast<int64_t>(tiles.x), b.counts + 1);
+  return hipGetLastError();
 }
 
-inline dim3 blocks_for(int64_t n, int t = 256) { return dim3(static_cast<unsigned>((n + t - 1) / t)); }
+template <typename KeyT>
+hipError_t run_items(const PlanSort& a, int64_t n_kept, int64_t n_items, const int32_t* perm, int2* fine, Item* items,
+                     hipStream_t s) {
+  const Scratch b = scratch_at(static_cast<char*>(a.scratch), a.nvis, sizeof(KeyT));
+  const KeyT* sorted = static_cast<const KeyT*>(b.key[passes_of(a.bits) & 1]);
+  hipLaunchKernelGGL(item_write<KeyT>, dim3(static_cast<unsigned>(tiles_of(a.nvis))),
+                     dim3(kSortThreads), 0, s, sorted, a.nvis, static_cast<KeyT>(a.drop_key),
+                     Divisor(static_cast<uint32_t>(a.os) * a.os), Divisor(static_cast<uint32_t>(a.max_chunk)), b.last_start, b.tile_items, a.nt, a.planes, items);
+  hipLaunchKernelGGL(plan_finish, dim3(static_cast<unsigned>((n_kept + 255) / 256)), dim3(256), 0, s, perm, b.fine_all,
+                     n_kept, fine, n_items, items);
+  return hipGetLastError();
+}
 
 }  // namespace
 
-hipError_t launch_plan_keys(const double* uvw, int64_t nvis, int n, double cell, int os, int nplanes,
-                            const double* w_planes, const PlaneInfo* planes, int nt, uint64_t drop_key,
-                            uint64_t* keys, int32_t* vals, int2* fine_all, hipStream_t s) {
-  if (nvis == 0) return hipSuccess;
-  const double ncell = static_cast<double>(n) * cell;
-  hipLaunchKernelGGL(plan_keys_kernel, blocks_for(nvis), dim3(256), 0, s, uvw, nvis, n, ncell, n / 2.0, os,
-                     nplanes, w_planes, planes, nt, drop_key, keys, vals, fine_all);
-  return hipGetLastError();
+size_t plan_scratch_bytes(int64_t nvis, int bits) { return scratch_at(nullptr, nvis, key_bytes_of(bits)).bytes; }
+
+hipError_t launch_plan_sort(const PlanSort& a, int32_t* perm, const int32_t** counts, hipStream_t s) {
+  *counts = scratch_at(static_cast<char*>(a.scratch), a.nvis, key_bytes_of(a.bits)).counts;
+  return a.bits <= 32 ? run_sort<uint32_t>(a, perm, s) : run_sort<uint64_t>(a, perm, s);
 }
 
-int64_t plan_scratch_elems(int64_t nvis) { return 4 * nvis + scan_scratch(nvis) + 64; }
-
-int64_t radix_scratch_elems(int64_t n) {
-  const int64_t blocks = (n + RS_TILE - 1) / RS_TILE;
-  return 256 * blocks + scan_scratch(256 * blocks) + 64;
-}
-
-hipError_t radix_sort_pairs(uint64_t* keys, int32_t* vals, uint64_t* keys_tmp, int32_t* vals_tmp, int64_t n,
-                            int bits, int32_t* scratch, int64_t scratch_elems, hipStream_t s,
-                            bool* result_in_tmp) {
-  *result_in_tmp = false;
-  if (n <= 1) return hipSuccess;
-  const int nblocks = static_cast<int>((n + RS_TILE - 1) / RS_TILE);
-  if (scratch_elems < radix_scratch_elems(n)) return hipErrorInvalidValue;
-  int32_t* hist = scratch;
-  int32_t* sscr = scratch + 256 * static_cast<int64_t>(nblocks);
-  uint64_t *ki = keys, *ko = keys_tmp;
-  int32_t *vi = vals, *vo = vals_tmp;
-  for (int shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(radix_hist, dim3(nblocks), dim3(RS_THREADS), 0, s, ki, n, shift, hist, nblocks);
-    hipError_t e = scan<OpSum>(hist, hist, 256 * static_cast<int64_t>(nblocks), false, sscr, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(radix_scatter, dim3(nblocks), dim3(RS_THREADS), 0, s, ki, vi, ko, vo, n, shift, hist,
-                       nblocks);
-    std::swap(ki, ko);
-    std::swap(vi, vo);
-    *result_in_tmp = !*result_in_tmp;
-  }
-  return hipGetLastError();
-}
-
-// Stage A: counts[0] = n_kept, counts[1] = n_items, counts[2] = n_runs on the device; `scratch`
-// keeps four int32 [nvis] arrays (run flags, run index / chunk offsets, run starts, chunks per run).
-hipError_t launch_plan_stage_a(const uint64_t* keys_sorted, int64_t nvis, uint64_t drop_key, int os,
-                               int max_chunk, int32_t* counts, int32_t* scratch, int64_t scratch_elems,
-                               hipStream_t s) {
-  if (nvis == 0) return hipSuccess;
-  if (scratch_elems < plan_scratch_elems(nvis)) return hipErrorInvalidValue;
-  int32_t* flag = scratch;
-  int32_t* idx = scratch + nvis;
-  int32_t* rstart = scratch + 2 * nvis;
-  int32_t* nchunk = scratch + 3 * nvis;
-  int32_t* sscr = scratch + 4 * nvis;
-  hipLaunchKernelGGL(count_kept, blocks_for(nvis), dim3(256), 0, s, keys_sorted, nvis, drop_key, counts);
-  hipLaunchKernelGGL(run_flags, blocks_for(nvis), dim3(256), 0, s, keys_sorted, nvis, counts, os, flag);
-  hipError_t e = scan<OpSum>(flag, idx, nvis, false, sscr, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(run_scatter, blocks_for(nvis), dim3(256), 0, s, flag, idx, nvis, rstart, counts);
-  hipLaunchKernelGGL(run_chunks, blocks_for(nvis), dim3(256), 0, s, rstart, nvis, counts, max_chunk, nchunk);
-  e = scan<OpSum>(nchunk, idx, nvis, false, sscr, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(item_total, dim3(1), dim3(1), 0, s, nchunk, idx, nvis, counts);
-  return hipGetLastError();
-}
-
-hipError_t launch_plan_scatter(const uint64_t* keys_sorted, const int32_t* perm, const int2* fine_all,
-                               int64_t n_kept, int64_t n_runs, int64_t nvis, int os, int nt, int max_chunk,
-                               const PlaneInfo* planes, const int32_t* scratch, int2* fine_sorted, Item* items,
-                               hipStream_t s) {
+hipError_t launch_plan_items(const PlanSort& a, int64_t n_kept, int64_t n_items, const int32_t* perm, int2* fine,
+                             Item* items, hipStream_t s) {
   if (n_kept == 0) return hipSuccess;
-  const int32_t* cidx = scratch + nvis;
-  const int32_t* rstart = scratch + 2 * nvis;
-  const int32_t* nchunk = scratch + 3 * nvis;
-  hipLaunchKernelGGL(fine_gather, blocks_for(n_kept), dim3(256), 0, s, perm, fine_all, n_kept, fine_sorted);
-  hipLaunchKernelGGL(item_write, blocks_for(n_runs), dim3(256), 0, s, keys_sorted, rstart, nchunk, cidx, n_runs,
-                     n_kept, os, nt, max_chunk, planes, items);
-  return hipGetLastError();
+    return a.bits <= 32 ? run_items<uint32_t>(a, n_kept, n_items, perm, fine, items, s)
+                      : run_items<uint64_t>(a, n_kept, n_items, perm, fine, items, s);
 }
 
 }  // namespace pg
