@@ -5,8 +5,9 @@
 // the coefficient vector is the eigenvector of the smallest eigenvalue of the
 // (symmetric, tridiagonal) matrix of the prolate differential operator
 //   -d/dx (1 - x^2) d/dx + c^2 x^2
-// in that basis (Bouwkamp 1947; Xiao, Rokhlin & Yarvin 2001).  The small dense
-// eigenproblem is solved with cyclic Jacobi rotations.
+// in that basis (Bouwkamp 1947; Xiao, Rokhlin & Yarvin 2001).  The matrix is positive definite and its
+// eigenvalues lie about c (2k + 1), k = 0, 2, 4, ... apart, so inverse iteration gains a factor of five
+// a step; 48 steps are far past rounding.  (Jacobi rotations of the dense matrix took milliseconds.)
 #include <cmath>
 #include <vector>
 
@@ -15,57 +16,43 @@
 namespace pg {
 namespace {
 
-// Eigenvector of the smallest eigenvalue of a symmetric matrix a[n*n] (destroyed).
-std::vector<double> smallest_eigenvector(std::vector<double>& a, int n) {
-  std::vector<double> v(static_cast<size_t>(n) * n, 0.0);
-  for (int i = 0; i < n; ++i) v[i * n + i] = 1.0;
-  for (int sweep = 0; sweep < 100; ++sweep) {
-    double off = 0.0;
-    for (int p = 0; p < n; ++p)
-      for (int q = p + 1; q < n; ++q) off += a[p * n + q] * a[p * n + q];
-    if (off < 1e-30) break;
-    for (int p = 0; p < n; ++p) {
-      for (int q = p + 1; q < n; ++q) {
-        double apq = a[p * n + q];
-        if (std::fabs(apq) < 1e-300) continue;
-        double theta = (a[q * n + q] - a[p * n + p]) / (2.0 * apq);
-        double t = (theta >= 0 ? 1.0 : -1.0) / (std::fabs(theta) + std::sqrt(theta * theta + 1.0));
-        double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
-        for (int k = 0; k < n; ++k) {  // columns p, q
-          double akp = a[k * n + p], akq = a[k * n + q];
-          a[k * n + p] = c * akp - s * akq;
-          a[k * n + q] = s * akp + c * akq;
-        }
-        for (int k = 0; k < n; ++k) {  // rows p, q
-          double apk = a[p * n + k], aqk = a[q * n + k];
-          a[p * n + k] = c * apk - s * aqk;
-          a[q * n + k] = s * apk + c * aqk;
-        }
-        for (int k = 0; k < n; ++k) {
-          double vkp = v[k * n + p], vkq = v[k * n + q];
-          v[k * n + p] = c * vkp - s * vkq;
-          v[k * n + q] = s * vkp + c * vkq;
-        }
-      }
-    }
+// Eigenvector of the smallest eigenvalue of the positive definite tridiagonal matrix with diagonal d
+// and off-diagonal e, by inverse iteration on its L D L^T factors.
+std::vector<double> smallest_eigenvector(std::vector<double> d, const std::vector<double>& e) {
+  const int n = static_cast<int>(d.size());
+  std::vector<double> l(n, 0.0), v(n, 0.0);
+  for (int i = 1; i < n; ++i) {
+    l[i] = e[i - 1] / d[i - 1];
+    d[i] -= l[i] * e[i - 1];
   }
-  int best = 0;
-  for (int i = 1; i < n; ++i)
-    if (a[i * n + i] < a[best * n + best]) best = i;
-  std::vector<double> out(n);
-  for (int k = 0; k < n; ++k) out[k] = v[k * n + best];
-  return out;
+  v[0] = 1.0;
+  for (int it = 0; it < 48; ++it) {
+    for (int i = 1; i < n; ++i) v[i] -= l[i] * v[i - 1];
+    for (int i = 0; i < n; ++i) v[i] /= d[i];
+    for (int i = n - 2; i >= 0; --i) v[i] -= l[i + 1] * v[i + 1];
+    double s = 0.0;
+    for (double x : v) s += x * x;
+    s = 1.0 / std::sqrt(s);
+    for (double& x : v) x *= s;
+  }
+  return v;
 }
 
-// sum_i coef[i] P_{2i}(x) by the Legendre three-term recurrence.
-double even_legendre_series(const std::vector<double>& coef, double x) {
-  double p0 = 1.0, p1 = x, sum = coef[0];
-  int deg_max = 2 * (static_cast<int>(coef.size()) - 1);
+// sum_i coef[i] P_{2i}(x) at every x, by the Legendre three-term recurrence (points in the inner loop:
+// they are independent, the degrees are a chain).
+std::vector<double> even_legendre_series(const std::vector<double>& coef, const std::vector<double>& x) {
+  const size_t m = x.size();
+  std::vector<double> p0(m, 1.0), p1(x), sum(m, coef[0]);
+  const int deg_max = 2 * (static_cast<int>(coef.size()) - 1);
   for (int k = 1; k < deg_max; ++k) {
-    double p2 = ((2.0 * k + 1.0) * x * p1 - k * p0) / (k + 1.0);
-    p0 = p1;
-    p1 = p2;
-    if ((k + 1) % 2 == 0) sum += coef[(k + 1) / 2] * p2;
+    const double a = (2.0 * k + 1.0) / (k + 1), b = static_cast<double>(k) / (k + 1);
+    const double c = (k + 1) % 2 == 0 ? coef[(k + 1) / 2] : 0.0;
+    for (size_t i = 0; i < m; ++i) {
+      const double p2 = a * x[i] * p1[i] - b * p0[i];
+      p0[i] = p1[i];
+      p1[i] = p2;
+      sum[i] += c * p2;
+    }
   }
   return sum;
 }
@@ -74,22 +61,17 @@ double even_legendre_series(const std::vector<double>& coef, double x) {
 
 std::vector<double> pswf0(double c, const std::vector<double>& x) {
   const int n = static_cast<int>(c) + 40;
-  std::vector<double> a(static_cast<size_t>(n) * n, 0.0);
+  std::vector<double> d(n), e(n - 1);
   for (int i = 0; i < n; ++i) {
-    double k = 2.0 * i;
-    a[i * n + i] = k * (k + 1) + c * c * (2 * k * (k + 1) - 1) / ((2 * k + 3) * (2 * k - 1));
-    if (i + 1 < n) {
-      double e = c * c * (k + 2) * (k + 1) / ((2 * k + 3) * std::sqrt((2 * k + 1) * (2 * k + 5)));
-      a[i * n + i + 1] = e;
-      a[(i + 1) * n + i] = e;
-    }
+    const double k = 2.0 * i;
+    d[i] = k * (k + 1) + c * c * (2 * k * (k + 1) - 1) / ((2 * k + 3) * (2 * k - 1));
+    if (i + 1 < n) e[i] = c * c * (k + 2) * (k + 1) / ((2 * k + 3) * std::sqrt((2 * k + 1) * (2 * k + 5)));
   }
-  std::vector<double> beta = smallest_eigenvector(a, n);
-  std::vector<double> coef(n);
-  for (int i = 0; i < n; ++i) coef[i] = beta[i] * std::sqrt(2.0 * i + 0.5);  // normalised -> plain basis
-  double norm = even_legendre_series(coef, 0.0);
-  std::vector<double> out(x.size());
-  for (size_t i = 0; i < x.size(); ++i) out[i] = even_legendre_series(coef, x[i]) / norm;
+  std::vector<double> coef = smallest_eigenvector(d, e);
+  for (int i = 0; i < n; ++i) coef[i] *= std::sqrt(2.0 * i + 0.5);  // normalised -> plain basis
+  std::vector<double> out = even_legendre_series(coef, x);
+  const double norm = even_legendre_series(coef, {0.0})[0];
+  for (double& v : out) v /= norm;
   return out;
 }
 
