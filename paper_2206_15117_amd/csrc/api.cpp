@@ -87,10 +87,10 @@ int make_kernels_impl(const pg_kernel_spec* spec, hipStream_t s, pg_kernels** ou
 
   const pg_geometry& g = spec->g;
   const int mk = g.mk, np = spec->npol, nqc = np * np;
-  std::vector<double> phi;
+  double beta[4];
   std::string err;
-  if (generate &&
-      !build_screens(np, spec->kind, spec->jones, spec->jones_b, mk, spec->eps_null, spec->stokes_convention, phi, err))
+  if (generate && !check_screens(np, spec->kind, spec->jones, spec->jones_b, mk, spec->eps_null, spec->stokes_convention,
+                                 beta, err))
     return fail(PG_EINVAL, err);
 
   auto* k = new (std::nothrow) pg_kernels();
@@ -126,11 +126,11 @@ int make_kernels_impl(const pg_kernel_spec* spec, hipStream_t s, pg_kernels** ou
 
   // Anti-aliasing function on the kernel lattice and at the image pixels.
   const double c = M_PI * g.aa_support / 2.0;
-  std::vector<double> xl(mk), xp(g.n);
-  for (int a = 0; a < mk; ++a) xl[a] = 2.0 * (a - mk / 2) / mk;
-  for (int j = 0; j < g.n; ++j) xp[j] = 2.0 * (j - g.n / 2) / g.n;
-  std::vector<double> aa_lat = pswf0(c, xl);
-  k->aa_pixels = pswf0(c, xp);
+  std::vector<double> x(mk + g.n);
+  for (int a = 0; a < mk; ++a) x[a] = 2.0 * (a - mk / 2) / mk;
+  for (int j = 0; j < g.n; ++j) x[mk + j] = 2.0 * (j - g.n / 2) / g.n;
+  const std::vector<double> aa = pswf0(c, x);
+  k->aa_pixels.assign(aa.begin() + mk, aa.end());
   std::vector<double> inv_aa(g.n);
   for (int j = 0; j < g.n; ++j) inv_aa[j] = 1.0 / k->aa_pixels[j];
 
@@ -152,27 +152,48 @@ int make_kernels_impl(const pg_kernel_spec* spec, hipStream_t s, pg_kernels** ou
 
   const size_t npix = static_cast<size_t>(mk) * mk;
   const size_t lmax = static_cast<size_t>(smax) * g.os;
-  DevBuf phi_d, aa_d, f_d, e_d, a_d, t_d;
+  // As many planes a round as fit the scratch of one plane with its screened cells and dense transform:
+  // three for 16 cells, and memory that a caller's allocator has to find stays what it was.
+  const size_t turns = lmax / 2 * (mk / 2 + 1);
+  const size_t per_plane = npix + turns + nqc * mk * lmax;
+  const size_t scratch = nqc * npix + lmax * mk + nqc * mk * lmax + nqc * lmax * lmax;
+  const int round = static_cast<int>(std::min<size_t>(std::min(g.nplanes, kGenPlanes), std::max<size_t>(1, scratch / per_plane)));
+  // The Jones fields land in the first-stage buffer: their screens are made before it is written.
+  const size_t field = 4 * npix;
+  const size_t half = std::max(round * nqc * mk * lmax, field * ((spec->jones ? 1 : 0) + (spec->jones_b ? 1 : 0)));
+  DevBuf phi_d, aa_d, w_d, e_d, a_d;
   if (!phi_d.alloc(sizeof(double2) * nqc * npix, s) || !aa_d.alloc(sizeof(double) * mk, s) ||
-      !f_d.alloc(sizeof(double2) * nqc * npix, s) || !e_d.alloc(sizeof(double2) * lmax * mk, s) ||
-      !a_d.alloc(sizeof(double2) * nqc * mk * lmax, s) || !t_d.alloc(sizeof(double2) * nqc * lmax * lmax, s))
+      !w_d.alloc(sizeof(double2) * round * npix, s) || !e_d.alloc(sizeof(double2) * round * turns, s) ||
+      !a_d.alloc(sizeof(double2) * half, s))
     return fail(PG_ENOMEM, "device allocation failed in make_kernels");
-  PG_HIP(hipMemcpyAsync(phi_d.p, phi.data(), phi.size() * sizeof(double), hipMemcpyHostToDevice, s), "upload screens");
-  PG_HIP(hipMemcpyAsync(aa_d.p, aa_lat.data(), mk * sizeof(double), hipMemcpyHostToDevice, s), "upload AA");
-  const double fov = g.n * g.cell;
-  for (int p = 0; p < g.nplanes; ++p) {
-    const int S = g.support[p];
-    const int len = S * g.os;
-    PG_HIP(launch_screen(phi_d.as<double2>(), aa_d.as<double>(), g.w_planes[p], fov, mk, nqc, f_d.as<double2>(), s), "screen");
-    PG_HIP(launch_twiddles(S, g.os, mk, e_d.as<double2>(), s), "twiddles");
-    // A[qc][b][dx] = sum_a F[qc][b][a] E[dx][a]
-    PG_HIP(launch_zgemm_nt(nqc, mk, len, mk, f_d.as<double2>(), npix, e_d.as<double2>(), 0, a_d.as<double2>(),
-                           static_cast<int64_t>(mk) * len, s), "dft stage 1");
-    // T[qc][dy][dx] = sum_b E[dy][b] A[qc][b][dx]
-    PG_HIP(launch_zgemm_nn(nqc, len, len, mk, e_d.as<double2>(), 0, a_d.as<double2>(), static_cast<int64_t>(mk) * len,
-                           t_d.as<double2>(), static_cast<int64_t>(len) * len, s), "dft stage 2");
-    void* dst = static_cast<char*>(k->table.p) + k->plane_offset[p] * entry;
-    PG_HIP(launch_pack(t_d.as<double2>(), S, g.os, nqc, spec->storage, dst, s), "pack");
+  double* jones = spec->jones ? a_d.as<double>() : nullptr;
+  double* jones_b = spec->jones_b ? a_d.as<double>() + (spec->jones ? 2 * field : 0) : nullptr;
+  if (jones) PG_HIP(hipMemcpyAsync(jones, spec->jones, sizeof(double2) * field, hipMemcpyHostToDevice, s), "upload Jones");
+  if (jones_b) PG_HIP(hipMemcpyAsync(jones_b, spec->jones_b, sizeof(double2) * field, hipMemcpyHostToDevice, s), "upload Jones");
+  PG_HIP(hipMemcpyAsync(aa_d.p, aa.data(), mk * sizeof(double), hipMemcpyHostToDevice, s), "upload AA");
+  PG_HIP(launch_screens(np, spec->kind, jones, jones_b, mk, beta, spec->stokes_convention, phi_d.as<double2>(), s), "screens");
+  GenRound r;
+  r.mk = mk;
+  r.nqc = nqc;
+  r.os = g.os;
+  r.support_max = smax;
+  r.storage = spec->storage;
+  r.ce = chunk_entries(spec->storage, nqc);
+  r.fov = g.n * g.cell;
+  r.aa = aa_d.as<double>();
+  r.phi = phi_d.as<double2>();
+  r.wterm = w_d.as<double2>();
+  r.twiddle = e_d.as<double2>();
+  r.half = a_d.as<double2>();
+  r.table = k->table.p;
+  for (int p0 = 0; p0 < g.nplanes; p0 += round) {
+    r.count = std::min(round, g.nplanes - p0);
+    for (int i = 0; i < r.count; ++i) {
+      r.support[i] = g.support[p0 + i];
+      r.offset[i] = k->plane_offset[p0 + i];
+      r.w[i] = g.w_planes[p0 + i];
+    }
+    PG_HIP(launch_tables(r, s), "tables");
   }
   PG_HIP(refresh_kernel_bound(k, 0, g.nplanes, s), "kernel bound");
   PG_HIP(hipStreamSynchronize(s), "make_kernels sync");

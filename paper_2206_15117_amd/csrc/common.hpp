@@ -169,14 +169,25 @@ struct pg_batch {
 namespace pg {
 
 // Kernel generation (kernels_gen.hip)
-hipError_t launch_screen(const double2* phi, const double* aa_lat, double w, double fov, int mk, int nqc,
-                         double2* out, hipStream_t s);
-hipError_t launch_twiddles(int support, int os, int mk, double2* e, hipStream_t s);
-hipError_t launch_zgemm_nt(int batch, int m, int n, int k, const double2* a, int64_t stride_a,
-                           const double2* b, int64_t stride_b, double2* c, int64_t stride_c, hipStream_t s);
-hipError_t launch_zgemm_nn(int batch, int m, int n, int k, const double2* a, int64_t stride_a,
-                           const double2* b, int64_t stride_b, double2* c, int64_t stride_c, hipStream_t s);
-hipError_t launch_pack(const double2* t, int support, int os, int nqc, int storage, void* table, hipStream_t s);
+// Kernel generation.  jones, jones_b: device copies of the fields or NULL.
+hipError_t launch_screens(int npol, int kind, const double* jones, const double* jones_b, int mk, const double beta[4],
+                          int convention, double2* phi, hipStream_t s);
+// Planes whose tables one round of launches makes, and the round's scratch arrays: per plane wterm
+// [mk][mk], twiddles [support os / 2][mk / 2 + 1] and first-stage products [nqc][mk][support os], each with the
+// stride of the set's largest support.
+constexpr int kGenPlanes = 8;
+struct GenRound {
+  int count, mk, nqc, os, support_max, storage, ce;
+  double fov;
+  const double* aa;     // [mk]
+  const double2* phi;   // [nqc][mk][mk]
+  double2 *wterm, *twiddle, *half;
+  void* table;
+  int support[kGenPlanes];
+  int64_t offset[kGenPlanes];  // first table entry
+  double w[kGenPlanes];
+};
+hipError_t launch_tables(const GenRound& r, hipStream_t s);
 
 // Plan (plan.hip)
 struct PlanSort {
@@ -228,8 +239,8 @@ hipError_t launch_batch_degrid(const pg_batch* b, int flags, hipStream_t s);
 
 // Host numerics (pswf.cpp, mueller.cpp)
 std::vector<double> pswf0(double c, const std::vector<double>& x);
-// Screens Phi[q][c][mk][mk] (complex, interleaved) for the given kind.
-bool build_screens(int npol, int kind, const double* jones, const double* jones_b, int mk, double eps, int convention,
-                   std::vector<double>& phi, std::string& err);
+// Whether the screens of the given kind exist at every lattice sample, and beta of Eq. 6 per diagonal entry.
+bool check_screens(int npol, int kind, const double* jones, const double* jones_b, int mk, double eps, int convention,
+                   double beta[4], std::string& err);
 
 }  // namespace pg

@@ -5,6 +5,7 @@
 // table the gridder reads.
 #include "common.hpp"
 #include "mlp.hpp"
+#include "mueller.hpp"
 
 namespace pg {
 namespace {
@@ -13,133 +14,221 @@ __device__ inline double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-__global__ void screen_kernel(const double2* __restrict__ phi, const double* __restrict__ aa, double w,
-                              double fov, int mk, int nqc, double2* __restrict__ out) {
+// phi[qc][px]: the screens at one lattice sample a thread.  The 4 x 4 solve is a chain of four pivots with
+// a double-precision division each; the samples are independent and the whole lattice of 256^2 takes
+// less than its 4 MB of Jones matrices takes to arrive.
+__global__ __launch_bounds__(64) void screens_kernel(int kind, const double* __restrict__ jones,
+                                                     const double* __restrict__ jones_b, size_t npix, double4 beta4,
+                                                     int convention, double2* __restrict__ phi) {
+  const size_t px = blockIdx.x * static_cast<size_t>(64) + threadIdx.x;
+  if (px >= npix) return;
+  const cd u = stokes_u(convention);
+  M4 m = mueller_at(jones, jones_b, npix, px, u);
+  M4 f;
+  if (kind == PG_KIND_GRID) {
+    const double beta[4] = {beta4.x, beta4.y, beta4.z, beta4.w};
+    regularise(m, beta);
+    f = stokes(convention);
+    solve(m, &f);
+  } else {  // (S^-1 M^S)^H
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      cd col[4], y[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) col[r] = m.a[r][c];
+      stokes_inverse_times(u, col, y);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) f.a[c][r] = conj(y[r]);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) phi[(q * 4 + c) * npix + px] = make_double2(f.a[q][c].re, f.a[q][c].im);
+}
+
+__global__ void unit_screen_kernel(size_t npix, double2* __restrict__ phi) {
+  const size_t px = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
+  if (px < npix) phi[px] = make_double2(1.0, 0.0);
+}
+
+// wterm[plane][b][a] = AA(l) AA(m) exp(-2 pi i w (n-1)), common to the plane's Mueller cells.
+__global__ void wterm_kernel(GenRound r) {
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
   const int b = blockIdx.y;
-  if (a >= mk) return;
-  const double step = fov / mk;
-  const double l = (a - mk / 2) * step, m = (b - mk / 2) * step;
+  if (a >= r.mk) return;
+  const double step = r.fov / r.mk;
+  const double l = (a - r.mk / 2) * step, m = (b - r.mk / 2) * step;
   const double r2 = l * l + m * m;
   const double nm1 = -r2 / (1.0 + sqrt(1.0 - r2));
   double s, c;
-  sincospi(2.0 * w * nm1, &s, &c);
-  const double g = aa[a] * aa[b];
-  const double2 scr = make_double2(g * c, -g * s);  // AA AA exp(-2 pi i w (n-1))
-  const size_t px = static_cast<size_t>(b) * mk + a;
-  const size_t npix = static_cast<size_t>(mk) * mk;
-  for (int qc = 0; qc < nqc; ++qc) out[qc * npix + px] = cmul(scr, phi[qc * npix + px]);
+  sincospi(2.0 * r.w[blockIdx.z] * nm1, &s, &c);
+  const double g = r.aa[a] * r.aa[b];
+  r.wterm[(static_cast<size_t>(blockIdx.z) * r.mk + b) * r.mk + a] = make_double2(g * c, -g * s);
 }
 
-// e[di][a] = exp(+2 pi i d (a - mk/2) / (os mk)) / mk with d = di - (S os/2 - 1); the last row
-// (d = S os / 2, outside the open footprint) is zero.
-__global__ void twiddle_kernel(int support, int os, int mk, double2* __restrict__ e) {
-  const int a = blockIdx.x * blockDim.x + threadIdx.x;
-  const int di = blockIdx.y;
-  if (a >= mk) return;
-  const int len = support * os;
-  double2 v = make_double2(0.0, 0.0);
-  if (di < len - 1) {
-    const long long d = di - (len / 2 - 1);
-    const long long period = 2LL * os * mk;  // exp(i pi x) has period 2 in x = num / (os mk)
-    long long num = (2LL * d * (a - mk / 2)) % period;
-    if (num < 0) num += period;
-    double s, c;
-    sincospi(static_cast<double>(num) / (static_cast<double>(os) * mk), &s, &c);
-    v = make_double2(c / mk, s / mk);
-  }
-  e[static_cast<size_t>(di) * mk + a] = v;
+// twiddle[plane][d][k] = (cos, sin)(2 pi d k / (os mk)) / mk for d = 0 .. S os/2 - 1, k = 0 .. mk/2.
+__global__ void twiddle_kernel(GenRound r) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x, d = blockIdx.y, mk = r.mk;
+  if (k > mk / 2 || d >= r.support[blockIdx.z] * r.os / 2) return;
+  const long long period = 2LL * r.os * mk;  // exp(i pi x) has period 2 in x = num / (os mk)
+  const long long num = (2LL * d * k) % period;
+  double s, c;
+  sincospi(static_cast<double>(num) / (static_cast<double>(r.os) * mk), &s, &c);
+  r.twiddle[(static_cast<size_t>(blockIdx.z) * (r.support_max * r.os / 2) + d) * (mk / 2 + 1) + k] =
+      make_double2(c / mk, s / mk);
 }
 
-// Batched complex float64 GEMM, C[m][n] = A[m][k] op(B); op(B) = B[k][n] (NN) or B[n][k]^T (NT).
-constexpr int BM = 32, BN = 32, BK = 16;
+// The separable zero-padded DFT as two float64 matrix products per plane and Mueller cell, contracted
+// over the lattice with e(d, a) = exp(+2 pi i d (a - mk/2) / (os mk)) / mk, d = di - (S os/2 - 1):
+//   stage 1  half[b][dx] = sum_a (wterm[b][a] phi[qc][b][a]) e(dx, a)
+//   stage 2  T[dy][dx]   = sum_b half[b][dx] e(dy, b), written to the table
+//     [phase_y][phase_x][chunk][tap_y][tap_x][e] (cell qc = chunk E + e; one 16-byte chunk of 64
+//     consecutive taps is 1 KiB of contiguous memory) at phase d mod os, tap d / os.
+// The last row and column (d = S os / 2, outside the open footprint) are zero.
+// Both are out[row][+-d] = C(row, d) +- i S(row, d) with C = sum_k even(row, k) cos(d, k),
+// S = sum_k odd(row, k) sin(d, k) over k = 0 .. mk/2, even and odd the sum and difference of the samples
+// k to either side of the lattice's middle: folding the samples and the outputs leaves a quarter of the
+// complex product's operations.
+// Bound: what is left of the float64 rate (16 FMA a clock and SIMD for vector and matrix instructions
+// alike) after the loads.  A vector FMA per lane needs its LDS operands per lane, twice the LDS's
+// bandwidth at 2 x 2 outputs a thread; v_mfma_f64_16x16x4 shares each among 16 lanes.  A workgroup takes 32 rows by 64
+// values of d, because the folded samples (two, in stage 1 with the w-term's two) cost four times the
+// bytes of the twiddles.  The next slice of the contraction is fetched into registers while one is used.
+// Screened cells and the dense transform are never stored: stage 1 multiplies the screen where it
+// stores it to LDS, stage 2 rounds into the table.
+// 24 planes of 16 cells, mk = 256, 1.4 ms, 88 us a
+// stage and round of three planes (75 us a stage and plane with vector FMAs on 32 x 32 tiles, unfolded, and 23 us
+// more for storing the screened cells and packing the transform).
+constexpr int kGenRows = 32, kGenCols = 64, kGenK = 16, kGenPitch = kGenK + 1;
+typedef double double4_t __attribute__((ext_vector_type(4)));
 
-template <bool BT>
-__global__ __launch_bounds__(256) void zgemm_kernel(int m, int n, int k, const double2* __restrict__ A,
-                                                    int64_t sa, const double2* __restrict__ B, int64_t sb,
-                                                    double2* __restrict__ C, int64_t sc) {
-  __shared__ double2 as[BK][BM + 1];
-  __shared__ double2 bs[BK][BN + 1];
-  const int z = blockIdx.z;
-  A += z * sa;
-  B += z * sb;
-  C += z * sc;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  double2 acc[2][2] = {};
-  for (int k0 = 0; k0 < k; k0 += BK) {
-    for (int idx = threadIdx.x; idx < BM * BK; idx += 256) {
-      int mm = idx / BK, kk = idx % BK;
-      int gm = m0 + mm, gk = k0 + kk;
-      as[kk][mm] = (gm < m && gk < k) ? A[static_cast<size_t>(gm) * k + gk] : make_double2(0.0, 0.0);
-    }
-    for (int idx = threadIdx.x; idx < BN * BK; idx += 256) {
-      int nn, kk;
-      if (BT) {
-        nn = idx / BK;
-        kk = idx % BK;
+template <int STAGE, typename TapT>
+__global__ __launch_bounds__(256) void table_kernel(GenRound r) {
+  const int mk = r.mk, mid = mk / 2, plane = blockIdx.z / r.nqc, qc = blockIdx.z % r.nqc;
+  const int len = r.support[plane] * r.os, len_max = r.support_max * r.os;
+  const int rows = STAGE == 1 ? mk : len, cols = len / 2;
+  const int m0 = blockIdx.y * kGenRows, n0 = blockIdx.x * kGenCols;
+  if (m0 >= rows || n0 >= cols) return;
+  const double2* twiddle = r.twiddle + static_cast<size_t>(plane) * (len_max / 2) * (mid + 1);
+  double2* half = r.half + static_cast<size_t>(blockIdx.z) * mk * len_max;
+  const double2* phi = r.phi + static_cast<size_t>(qc) * mk * mk;
+  const double2* wterm = r.wterm + static_cast<size_t>(plane) * mk * mk;
+  __shared__ double fold[4][kGenRows * kGenPitch];  // even re, even im, odd re, odd im: [row][k]
+  __shared__ double turn[2][kGenCols * kGenPitch];  // cos, sin: [d][k]
+
+  const int t = threadIdx.x;
+  const double2 zero = make_double2(0.0, 0.0);
+  // Thread t holds rows / columns t / 16 + 16 i of sample t mod 16, so that 16 lanes read along the
+  // contraction; stage 2's samples run along its rows: row t mod 32 of samples t / 32 + 8 i.
+  double2 plus[2], minus[2], wplus[2], wminus[2], tw[4];
+  const auto fetch = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = m0 + (STAGE == 1 ? t / kGenK + 16 * i : t % kGenRows);
+      const int k = k0 + (STAGE == 1 ? t % kGenK : t / kGenRows + 8 * i);
+      const bool inp = row < rows && k < mid, inm = row < rows && k >= 1 && k <= mid;
+      if (STAGE == 1) {
+        const size_t o = static_cast<size_t>(row) * mk + mid;
+        plus[i] = inp ? phi[o + k] : zero;
+        minus[i] = inm ? phi[o - k] : zero;
+        wplus[i] = inp ? wterm[o + k] : zero;
+        wminus[i] = inm ? wterm[o - k] : zero;
       } else {
-        kk = idx / BN;
-        nn = idx % BN;
+        plus[i] = inp ? half[static_cast<size_t>(mid + k) * len_max + row] : zero;
+        minus[i] = inm ? half[static_cast<size_t>(mid - k) * len_max + row] : zero;
       }
-      int gn = n0 + nn, gk = k0 + kk;
-      double2 v = make_double2(0.0, 0.0);
-      if (gn < n && gk < k) v = BT ? B[static_cast<size_t>(gn) * k + gk] : B[static_cast<size_t>(gk) * n + gn];
-      bs[kk][nn] = v;
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int d = n0 + t / kGenK + 16 * i, k = k0 + t % kGenK;
+      tw[i] = (d < cols && k <= mid) ? twiddle[static_cast<size_t>(d) * (mid + 1) + k] : zero;
+    }
+  };
+  const auto store = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int o = STAGE == 1 ? (t / kGenK + 16 * i) * kGenPitch + t % kGenK
+                               : (t % kGenRows) * kGenPitch + t / kGenRows + 8 * i;
+      const double2 p = STAGE == 1 ? cmul(wplus[i], plus[i]) : plus[i];
+      const double2 m = STAGE == 1 ? cmul(wminus[i], minus[i]) : minus[i];
+      fold[0][o] = p.x + m.x;
+      fold[1][o] = p.y + m.y;
+      fold[2][o] = p.x - m.x;
+      fold[3][o] = p.y - m.y;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int o = (t / kGenK + 16 * i) * kGenPitch + t % kGenK;
+      turn[0][o] = tw[i].x;
+      turn[1][o] = tw[i].y;
+    }
+  };
+
+  const int lane = t % 64, wave = t / 64;
+  const int row0 = 16 * (wave / 2), col0 = 32 * (wave % 2);
+  const int of = (row0 + lane % 16) * kGenPitch + lane / 16;
+  const int ot = (col0 + lane % 16) * kGenPitch + lane / 16;
+  const int tiles = (cols - n0 - col0 + 15) / 16;  // 16-column tiles of this wave that hold a column
+  double4_t cr[2] = {}, ci[2] = {}, sr[2] = {}, si[2] = {};
+  fetch(0);
+  for (int k0 = 0; k0 <= mid; k0 += kGenK) {
+    store();
     __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < BK; ++kk) {
-      double2 a0 = as[kk][ty], a1 = as[kk][ty + 16];
-      double2 b0 = bs[kk][tx], b1 = bs[kk][tx + 16];
-      double2 av[2] = {a0, a1}, bv[2] = {b0, b1};
+    if (k0 + kGenK <= mid) fetch(k0 + kGenK);
+    const int steps = min(kGenK, mid + 1 - k0);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int k = 0; k < kGenK; k += 4) {
+      if (k >= steps) break;
+      const double er = fold[0][of + k], ei = fold[1][of + k], dr = fold[2][of + k], di = fold[3][of + k];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          acc[i][j].x = fma(av[i].x, bv[j].x, fma(-av[i].y, bv[j].y, acc[i][j].x));
-          acc[i][j].y = fma(av[i].x, bv[j].y, fma(av[i].y, bv[j].x, acc[i][j].y));
-        }
+      for (int j = 0; j < 2; ++j) {
+        if (j >= tiles) break;
+        const double c = turn[0][ot + 16 * j * kGenPitch + k], s = turn[1][ot + 16 * j * kGenPitch + k];
+        cr[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(er, c, cr[j], 0, 0, 0);
+        ci[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ei, c, ci[j], 0, 0, 0);
+        sr[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(dr, s, sr[j], 0, 0, 0);
+        si[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(di, s, si[j], 0, 0, 0);
+      }
     }
     __syncthreads();
   }
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) {
-      int gm = m0 + ty + 16 * i, gn = n0 + tx + 16 * j;
-      if (gm < m && gn < n) C[static_cast<size_t>(gm) * n + gn] = acc[i][j];
-    }
-}
 
-// Table layout per plane: [phase_y][phase_x][chunk][tap_y][tap_x][e], entry (q, c) = chunk * E + e,
-// so that one 16-byte chunk of 64 consecutive taps is 1 KiB of contiguous memory.
-//   table entry = T[qc][ph_y + t_y os][ph_x + t_x os]
-__global__ void pack_kernel(const double2* __restrict__ t, int support, int os, int nqc, int storage, int ce,
-                            void* __restrict__ table) {
-  const size_t len = static_cast<size_t>(support) * os;
-  const size_t ss = static_cast<size_t>(support) * support;
-  const size_t nch = nqc / ce;
-  const size_t total = ss * os * os * nqc;
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < total;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x) {
-    const size_t e = i % ce;
-    size_t r = i / ce;
-    const size_t tap = r % ss;
-    r /= ss;
-    const size_t ch = r % nch;
-    const size_t phase = r / nch;
-    const size_t qc = ch * ce + e;
-    const size_t ty = tap / support, tx = tap % support;
-    const size_t py = phase / os, px = phase % os;
-    const double2 v = t[(qc * len + py + ty * os) * len + px + tx * os];
-    if (storage == PG_STORE_F16) {
+  // out[row][d + S os/2 - 1]
+  const auto put = [&](int row, int di, double re, double im) {
+    if (STAGE == 1) {
+      half[static_cast<size_t>(row) * len_max + di] = make_double2(re, im);
+      return;
+    }
+    const int S = r.support[plane], os = r.os;
+    const size_t chunk = static_cast<size_t>((di % os) * os + row % os) * (r.nqc / r.ce) + qc / r.ce;
+    const size_t tap = static_cast<size_t>(di / os) * S + row / os;
+    TapT* out = static_cast<TapT*>(r.table) + r.offset[plane] + (chunk * S * S + tap) * r.ce + qc % r.ce;
+    if constexpr (sizeof(TapT) == 4) {
       // direct float64 -> float16 rounding (no intermediate float32 rounding)
-      const _Float16 re = static_cast<_Float16>(v.x), im = static_cast<_Float16>(v.y);
-      __half hr, hi;
-      __builtin_memcpy(&hr, &re, 2);
-      __builtin_memcpy(&hi, &im, 2);
-      static_cast<__half2*>(table)[i] = __halves2half2(hr, hi);
+      const _Float16 hr = static_cast<_Float16>(re), hi = static_cast<_Float16>(im);
+      __half2 h;
+      __builtin_memcpy(&h.x, &hr, 2);
+      __builtin_memcpy(&h.y, &hi, 2);
+      *out = h;
     } else {
-      static_cast<float2*>(table)[i] = make_float2(static_cast<float>(v.x), static_cast<float>(v.y));
+      *out = make_float2(static_cast<float>(re), static_cast<float>(im));
+    }
+  };
+  // Results of the float64 instruction: lane holds column lane mod 16 of rows lane / 16 + 4 i.
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int d = n0 + col0 + 16 * j + lane % 16;
+    if (d >= cols) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = m0 + row0 + lane / 16 + 4 * i;
+      if (row >= rows) continue;
+      put(row, cols - 1 + d, cr[j][i] - si[j][i], ci[j][i] + sr[j][i]);
+      if (d > 0)
+        put(row, cols - 1 - d, cr[j][i] + si[j][i], ci[j][i] - sr[j][i]);
+      else
+        put(row, len - 1, 0.0, 0.0);
     }
   }
 }
@@ -187,33 +276,47 @@ __global__ void cell_io_kernel(void* __restrict__ table, int storage, int nqc, i
 }
 
 // kbound[4 p + q] = max over the entries of Mueller row q in plane p's table of |re| + |im|, the
-// bound the shared-tap gridder scales its fixed point from.  Block b takes phase b / nch, chunk
-// b mod nch of the plane: entries [b ss E, (b + 1) ss E), entry i of it is tap i / E, Mueller cell
-// chunk E + i mod E.  Per-thread maxima per row q, then a wave maximum and one integer atomic max
-// on the float bits per wave (non-negative floats order like their bits).
+// bound the shared-tap gridder scales its fixed point from.  A plane's table is os^2 phases of nch chunks
+// of ss E entries, entry i of a chunk being tap i / E, Mueller cell chunk E + i mod E.  One pass over
+// the tables, bounded by reading them: blockIdx.y is the plane, and at most 64 blocks walk its chunks,
+// each with one integer atomic max a row at its end (non-negative floats order like their bits).  (One
+// block and 16 atomics for each chunk queued at four addresses: 28 us a plane, now 66 us for 24.)
 __device__ inline float2 entry_value(float2 t) { return t; }
 __device__ inline float2 entry_value(__half2 t) { return __half22float2(t); }
 
 template <typename TapT>
-__global__ __launch_bounds__(256) void kernel_bound_kernel(const TapT* __restrict__ plane_table, int ss, int e_per_chunk,
-                                                           int nch, int npol, unsigned* __restrict__ out) {
-  const int chunk = static_cast<int>(blockIdx.x % static_cast<unsigned>(nch));
-  const TapT* blk = plane_table + static_cast<size_t>(blockIdx.x) * ss * e_per_chunk;
+__global__ __launch_bounds__(256) void kernel_bound_kernel(const TapT* __restrict__ table,
+                                                           const PlaneInfo* __restrict__ planes, int plane0, int os,
+                                                           int e_per_chunk, int nch, int npol, unsigned* __restrict__ out) {
+  const int plane = plane0 + blockIdx.y;
+  const int per_chunk = planes[plane].support * planes[plane].support * e_per_chunk;
+  table += planes[plane].offset;
   float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int i = threadIdx.x; i < ss * e_per_chunk; i += 256) {
-    const int q = (chunk * e_per_chunk + (i & (e_per_chunk - 1))) / npol;
-    const float2 t = entry_value(blk[i]);
-    const float a = fabsf(t.x) + fabsf(t.y);
+  for (int c = blockIdx.x; c < os * os * nch; c += gridDim.x) {
+    const TapT* blk = table + static_cast<size_t>(c) * per_chunk;
+    const int cell0 = c % nch * e_per_chunk;
+    for (int i = threadIdx.x; i < per_chunk; i += 256) {
+      const int q = (cell0 + (i & (e_per_chunk - 1))) / npol;
+      const float2 t = entry_value(blk[i]);
+      const float a = fabsf(t.x) + fabsf(t.y);
 #pragma unroll
-    for (int qq = 0; qq < 4; ++qq)
-      if (qq == q) m[qq] = fmaxf(m[qq], a);
+      for (int qq = 0; qq < 4; ++qq)
+        if (qq == q) m[qq] = fmaxf(m[qq], a);
+    }
   }
+  __shared__ float best[4][4];
 #pragma unroll
   for (int qq = 0; qq < 4; ++qq) {
     float v = m[qq];
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v = fmaxf(v, __shfl_xor(v, d, 64));
-    if ((threadIdx.x & 63) == 0 && v > 0.0f) atomicMax(out + qq, __float_as_uint(v));
+    if ((threadIdx.x & 63) == 0) best[qq][threadIdx.x >> 6] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    const float* v = best[threadIdx.x];
+    const float top = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+    if (top > 0.0f) atomicMax(out + 4 * plane + threadIdx.x, __float_as_uint(top));
   }
 }
 
@@ -229,30 +332,31 @@ hipError_t cell_io(void* table, int storage, int nqc, int ce, int os, int suppor
   return hipGetLastError();
 }
 
-hipError_t launch_screen(const double2* phi, const double* aa_lat, double w, double fov, int mk, int nqc,
-                         double2* out, hipStream_t s) {
-  dim3 grid((mk + 127) / 128, mk);
-  hipLaunchKernelGGL(screen_kernel, grid, dim3(128), 0, s, phi, aa_lat, w, fov, mk, nqc, out);
+hipError_t launch_screens(int npol, int kind, const double* jones, const double* jones_b, int mk, const double beta[4],
+                          int convention, double2* phi, hipStream_t s) {
+  const size_t npix = static_cast<size_t>(mk) * mk;
+  if (npol == 1) {
+    hipLaunchKernelGGL(unit_screen_kernel, dim3(static_cast<unsigned>((npix + 255) / 256)), dim3(256), 0, s, npix, phi);
+  } else {
+    hipLaunchKernelGGL(screens_kernel, dim3(static_cast<unsigned>((npix + 63) / 64)), dim3(64), 0, s, kind, jones, jones_b,
+                       npix, make_double4(beta[0], beta[1], beta[2], beta[3]), convention, phi);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_twiddles(int support, int os, int mk, double2* e, hipStream_t s) {
-  dim3 grid((mk + 127) / 128, support * os);
-  hipLaunchKernelGGL(twiddle_kernel, grid, dim3(128), 0, s, support, os, mk, e);
-  return hipGetLastError();
-}
-
-hipError_t launch_zgemm_nt(int batch, int m, int n, int k, const double2* a, int64_t stride_a,
-                           const double2* b, int64_t stride_b, double2* c, int64_t stride_c, hipStream_t s) {
-  dim3 grid((n + BN - 1) / BN, (m + BM - 1) / BM, batch);
-  hipLaunchKernelGGL(zgemm_kernel<true>, grid, dim3(256), 0, s, m, n, k, a, stride_a, b, stride_b, c, stride_c);
-  return hipGetLastError();
-}
-
-hipError_t launch_zgemm_nn(int batch, int m, int n, int k, const double2* a, int64_t stride_a,
-                           const double2* b, int64_t stride_b, double2* c, int64_t stride_c, hipStream_t s) {
-  dim3 grid((n + BN - 1) / BN, (m + BM - 1) / BM, batch);
-  hipLaunchKernelGGL(zgemm_kernel<false>, grid, dim3(256), 0, s, m, n, k, a, stride_a, b, stride_b, c, stride_c);
+hipError_t launch_tables(const GenRound& r, hipStream_t s) {
+  const unsigned len = static_cast<unsigned>(r.support_max * r.os), mk = static_cast<unsigned>(r.mk);
+  const unsigned count = static_cast<unsigned>(r.count), cells = count * r.nqc;
+  const auto ceil_div = [](unsigned n, unsigned d) { return (n + d - 1) / d; };
+  const unsigned cols = ceil_div(len / 2, kGenCols);
+  hipLaunchKernelGGL(wterm_kernel, dim3(ceil_div(mk, 128), mk, count), dim3(128), 0, s, r);
+  hipLaunchKernelGGL(twiddle_kernel, dim3(ceil_div(mk / 2 + 1, 128), len / 2, count), dim3(128), 0, s, r);
+  hipLaunchKernelGGL((table_kernel<1, float2>), dim3(cols, ceil_div(mk, kGenRows), cells), dim3(256), 0, s, r);
+  const dim3 grid(cols, ceil_div(len, kGenRows), cells);
+  if (r.storage == PG_STORE_F16)
+    hipLaunchKernelGGL((table_kernel<2, __half2>), grid, dim3(256), 0, s, r);
+  else
+    hipLaunchKernelGGL((table_kernel<2, float2>), grid, dim3(256), 0, s, r);
   return hipGetLastError();
 }
 
@@ -262,28 +366,19 @@ hipError_t refresh_kernel_bound(pg_kernels* k, int plane0, int nplanes, hipStrea
   if (e != hipSuccess) return e;
   const int nqc = k->npol * k->npol;
   const int ec = chunk_entries(k->storage, nqc), nch = nqc / ec;
-  for (int p = plane0; p < plane0 + nplanes; ++p) {
-    const unsigned blocks = static_cast<unsigned>(k->os * k->os * nch);
-    unsigned* out = reinterpret_cast<unsigned*>(k->kbound.as<float>() + 4 * p);
-    const int ss = k->support[p] * k->support[p];
+  unsigned* out = k->kbound.as<unsigned>();
+  for (int p = 0; p < nplanes; p += 65535) {
+    const dim3 grid(static_cast<unsigned>(std::min(k->os * k->os * nch, 64)), static_cast<unsigned>(std::min(nplanes - p, 65535)));
     if (k->storage == PG_STORE_F16)
-      hipLaunchKernelGGL(kernel_bound_kernel<__half2>, dim3(blocks), dim3(256), 0, s,
-                         k->table.as<__half2>() + k->plane_offset[p], ss, ec, nch, k->npol, out);
+      hipLaunchKernelGGL(kernel_bound_kernel<__half2>, grid, dim3(256), 0, s, k->table.as<__half2>(),
+                         k->planes.as<PlaneInfo>(), plane0 + p, k->os, ec, nch, k->npol, out);
     else
-      hipLaunchKernelGGL(kernel_bound_kernel<float2>, dim3(blocks), dim3(256), 0, s,
-                         k->table.as<float2>() + k->plane_offset[p], ss, ec, nch, k->npol, out);
+      hipLaunchKernelGGL(kernel_bound_kernel<float2>, grid, dim3(256), 0, s, k->table.as<float2>(),
+                         k->planes.as<PlaneInfo>(), plane0 + p, k->os, ec, nch, k->npol, out);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-hipError_t launch_pack(const double2* t, int support, int os, int nqc, int storage, void* table, hipStream_t s) {
-  size_t total = static_cast<size_t>(support) * os * support * os * nqc;
-  int blocks = static_cast<int>(std::min<size_t>((total + 255) / 256, 65535));
-  hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, s, t, support, os, nqc, storage,
-                     chunk_entries(storage, nqc), table);
-  return hipGetLastError();
 }
 
 }  // namespace pg
