@@ -1075,30 +1075,31 @@ __device__ __forceinline__ void degrid_sum_rows(float (&acc)[R][2 * NC], int j, 
 // tile), degridded together: every tap is loaded once and applied to all R rows, whose sub-grid
 // positions differ by a wave-uniform offset.  One 64-lane sum per row and output value; lane 63
 // writes the rows' visibilities.
+// Bound: vector instruction issue (the loop is 92 to 95 % FMAs, 64 a row and 64 taps), at the four waves a
+// SIMD that four planes of sub-grid in LDS leave.  Runs in a wave are three to five rows long at 300 rows an item, so every length
+// up to the longest has its own pass: a run of 7 taken as 4 + 2 + 1 loaded its taps three times.  2.3 M rows,
+// 2048^2: 2.31 ms, 2.49 with passes of 8, 4, 2 and 1.  (The same sums on v_mfma_f32_4x4x1 took 2.9 ms: pairs of rows
+// and 16 taps an instruction leave too few products to hide a step's loads behind.)
 constexpr int kDegridRun = 8;  // longest run of same-phase rows whose tap loads one degrid pass shares
 
 template <int NP, typename TapT, int R, int NC = NP>
-__device__ __forceinline__ void degrid_rows(const float2* lds, const TapT* phase_table, int j, int m_ly, int m_lx,
-                                            int m_k, int S, int SS, int P, int WP, float inv_s,
-                                            const FootStep& step, float2* __restrict__ vis_out, int flags,
-                                            int lane, int c0 = 0) {
+__device__ __forceinline__ void degrid_rows(const float2* lds, const TapT* phase_table, int j, int m_cell, int m_k, int SS,
+                                            int WP, const FootStep& step, TapCursor cur, float2* __restrict__ vis_out,
+                                            int flags, int lane, int c0 = 0) {
   // NC < NP: this workgroup computes correlations c0 .. c0 + NC - 1, from Mueller entries (q, c0 ..)
   // which sit in every (NP / NC)-th 16-byte chunk of the phase block
   const TapChunks<NP * NC, TapT> tc = NC == NP ? TapChunks<NP * NC, TapT>(phase_table, SS)
                                                : TapChunks<NP * NC, TapT>(phase_table, SS, c0 / NC, NP / NC);
   const float2* lds_hi = lds + 2 * WP;  // planes (2, 3) of the plane-pair layout
-  const int ly0 = __builtin_amdgcn_readlane(m_ly, j), lx0 = __builtin_amdgcn_readlane(m_lx, j);
   int d[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r)
-    d[r] = (__builtin_amdgcn_readlane(m_ly, j + r) - ly0) * P + (__builtin_amdgcn_readlane(m_lx, j + r) - lx0);
+  for (int r = 0; r < R; ++r) d[r] = __builtin_amdgcn_readlane(m_cell, j + r);
   float acc[R][2 * NC];
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
     for (int c = 0; c < 2 * NC; ++c) acc[r][c] = 0.0f;
   constexpr uint32_t TB = TapChunks<NP * NC, TapT>::kTapBytes;
-  TapCursor cur(lane, ly0, lx0, inv_s, S, P);
   uint32_t boff = static_cast<uint32_t>(lane) * TB;
 #pragma unroll(R == 1 ? 2 : 1)
   for (int t = lane; t < SS; t += 64) {
@@ -1154,7 +1155,6 @@ __device__ __forceinline__ void degrid_item(const Item it, const int2* __restric
   float2* lds = reinterpret_cast<float2*>(lds_f);  // plane pairs: [q / 2][W][P][q % 2]
   const PlaneInfo pl = planes[it.plane];
   const int S = pl.support, W = pl.width, P = pl.pitch, WP = W * P, SS = S * S, half = S * os / 2;
-  const float inv_s = 1.0f / static_cast<float>(S);
   const bool shift = (flags & PG_FFTSHIFT) != 0;
   const size_t pstride = static_cast<size_t>(n) * n;
   // sub-grid fill: kFill cells per thread per pass, all their loads issued before the first LDS
@@ -1189,50 +1189,56 @@ __device__ __forceinline__ void degrid_item(const Item it, const int2* __restric
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const FootStep step(S, P);
+  const TapCursor start(lane, 0, 0, 1.0f / static_cast<float>(S), S, P);
   // wave w takes a contiguous run of the item's rows, so rows of one phase stay together; their
   // metadata comes in 64 at a time by one coalesced load and is broadcast per row with readlane
   const int per = (it.end - it.start + NW - 1) / NW;
   const int w0 = it.start + wave * per, w1 = min(it.end, w0 + per);
   for (int blk = w0; blk < w1; blk += 64) {
     const int mine = blk + lane;
-    int m_ly = 0, m_lx = 0, m_ph = -1, m_k = 0;
+    int m_cell = 0, m_ph = -1, m_k = 0;
     if (mine < w1) {
       const int2 f = fine[mine];
       const int x0 = ceil_div_i(f.x - half + 1, os), y0 = ceil_div_i(f.y - half + 1, os);
-      m_ly = y0 - it.oy;
-      m_lx = x0 - it.ox;
+      m_cell = (y0 - it.oy) * P + x0 - it.ox;
       m_ph = (y0 * os - f.y + half - 1) * os + (x0 * os - f.x + half - 1);
       m_k = perm[mine];
     }
     const int nrow = min(64, w1 - blk);
+    // first rows of the runs of one phase (the lanes past the last row, phase -1, start one too)
+    const int before = __shfl_up(m_ph, 1, 64);
+    const uint64_t starts = __ballot(lane == 0 || m_ph != before);
     for (int j = 0; j < nrow;) {
-      const int ph = __builtin_amdgcn_readlane(m_ph, j);
-      int run = 1;  // rows from j on with the same phase, up to kDegridRun
-      while (run < kDegridRun && j + run < nrow && __builtin_amdgcn_readlane(m_ph, j + run) == ph) ++run;
-      run = __builtin_amdgcn_readfirstlane(run);
-      const TapT* pt = table + pl.offset + static_cast<size_t>(ph) * SS * NP * NP;
-      if (kDegridRun >= 8 && run == 8) {
-        degrid_rows<NP, TapT, 8, NC>(lds, pt, j, m_ly, m_lx, m_k, S, SS, P, WP, inv_s, step, vis_out, flags, lane,
-                                    c0);
-      } else if (run >= 4) {
-        run = 4;
-        degrid_rows<NP, TapT, 4, NC>(lds, pt, j, m_ly, m_lx, m_k, S, SS, P, WP, inv_s, step, vis_out, flags, lane,
-                                    c0);
-      } else if (run >= 2) {
-        degrid_rows<NP, TapT, 2, NC>(lds, pt, j, m_ly, m_lx, m_k, S, SS, P, WP, inv_s, step, vis_out, flags, lane,
-                                    c0);
-        run = 2;
-      } else {
-        degrid_rows<NP, TapT, 1, NC>(lds, pt, j, m_ly, m_lx, m_k, S, SS, P, WP, inv_s, step, vis_out, flags, lane,
-                                    c0);
+      // what is left of the run, in as few passes as hold it, of even lengths
+      const uint64_t rest = (starts >> j) >> 1;
+      int run = rest ? __builtin_ctzll(rest) + 1 : 64 - j;
+      if (run > kDegridRun) {
+        const int passes = (run + kDegridRun - 1) / kDegridRun;
+        run = (run + passes - 1) / passes;
+      }
+      const TapT* pt = table + pl.offset + static_cast<size_t>(__builtin_amdgcn_readlane(m_ph, j)) * SS * NP * NP;
+      const auto rows = [&](auto r) {
+        degrid_rows<NP, TapT, decltype(r)::value, NC>(lds, pt, j, m_cell, m_k, SS, WP, step, start, vis_out, flags, lane,
+                                                      c0);
+      };
+      switch (run) {
+        case 1: rows(std::integral_constant<int, 1>()); break;
+        case 2: rows(std::integral_constant<int, 2>()); break;
+        case 3: rows(std::integral_constant<int, 3>()); break;
+        case 4: rows(std::integral_constant<int, 4>()); break;
+        case 5: rows(std::integral_constant<int, 5>()); break;
+        case 6: rows(std::integral_constant<int, 6>()); break;
+        case 7: rows(std::integral_constant<int, 7>()); break;
+        default: rows(std::integral_constant<int, 8>()); break;
       }
       j += run;
     }
   }
 }
 
+// four waves a SIMD: the launches put 16 waves on a CU, in one to four workgroups
 template <int NP, typename TapT, int NW, int NC = NP>
-__global__ __launch_bounds__(NW * 64) void degrid_kernel(const Item* __restrict__ items,
+__global__ __launch_bounds__(NW * 64, 4) void degrid_kernel(const Item* __restrict__ items,
                                                          const int2* __restrict__ fine,
                                                          const int32_t* __restrict__ perm,
                                                          const TapT* __restrict__ table,
@@ -1250,7 +1256,7 @@ __global__ __launch_bounds__(NW * 64) void degrid_kernel(const Item* __restrict_
 }
 
 template <int NP, typename TapT, int NW>
-__global__ __launch_bounds__(NW * 64) void degrid_batch(const FieldArgs* __restrict__ fields,
+__global__ __launch_bounds__(NW * 64, 4) void degrid_batch(const FieldArgs* __restrict__ fields,
                                                         const int2* __restrict__ work, int flags) {
   extern __shared__ float lds_f[];
   const int2 wr = work[blockIdx.x];
