@@ -1324,6 +1324,20 @@ hipError_t run_grid_banded(const pg_plan* p, const pg_kernels* k, const float2* 
   return hipGetLastError();
 }
 
+// Workgroups of one item that an XCD takes in a row when each computes NQ of its planes from its own rows
+// of the Mueller tables: as many as the plan's group asks for, but no more than keep a plane's table in the XCD's 4 MB of
+// L2, half of them until it fits.  A set of larger supports reads its tables from beyond L2 otherwise: 6 M rows on 4096^2
+// with one plane a workgroup and 3.3 MB a plane and part, 26.5 ms in groups of four, 21.0 of two, 18.1 of one.
+// Where two parts fit, sharing an item's visibilities is worth more: 0.70 M rows on 1500^2 at 1.1 MB, 0.80 ms, 0.83
+// and 0.90; 2.3 M rows on 2048^2 at 1.9 MB, 2.68, 2.56 and 2.58.
+template <int NP, int NQ>
+int shared_group(const pg_plan* p, const pg_kernels* k) {
+  const size_t part = k->table.bytes / k->nplanes / (NP / NQ);
+  int group = p->xcd_group;
+  while (NQ < NP && group > 1 && std::min(group, NP / NQ) * part > (size_t{4} << 20)) group /= 2;
+  return group;
+}
+
 template <int NP, typename TapT, int NW, int NQ = NP>
 hipError_t run_grid_shared(const pg_plan* p, const pg_kernels* k, const float2* vis, float2* grid, int flags,
                            hipStream_t s) {
@@ -1332,10 +1346,11 @@ hipError_t run_grid_shared(const pg_plan* p, const pg_kernels* k, const float2* 
   const size_t bytes = sub + kSharedScratch;
   hipError_t e = allow_lds(fn, bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(fn, dim3(xcd_blocks(p->n_items * (NP / NQ), p->xcd_group)), dim3(NW * 64), bytes, s,
+  const int group = shared_group<NP, NQ>(p, k);
+  hipLaunchKernelGGL(fn, dim3(xcd_blocks(p->n_items * (NP / NQ), group)), dim3(NW * 64), bytes, s,
                      p->items.as<Item>(), p->fine.as<int2>(), p->perm.as<int32_t>(), vis, k->table.as<TapT>(),
                      k->planes.as<PlaneInfo>(), k->kbound.as<float>(), k->os, k->n, grid, flags,
-                     static_cast<int>(sub), static_cast<int>(p->n_items), p->xcd_group);
+                     static_cast<int>(sub), static_cast<int>(p->n_items), group);
   return hipGetLastError();
 }
 
