@@ -1,6 +1,6 @@
 // Hogbom minor cycle of Cotton-Schwab clean (Sec. 2.1), entirely on the device.
 //
-// The image is cut into at most kCleanTiles tiles; the largest key of every tile (|I| over the masked
+// The image is cut into at most kCleanTilesSide^2 tiles; the largest key of every tile (|I| over the masked
 // pixels packed with the inverted pixel index into 64 bits: the largest |I| wins, ties go to the
 // lowest index) is kept from one iteration to the next.  One iteration is one launch, one workgroup
 // per tile, that never returns to the host:
