@@ -29,7 +29,7 @@ __global__ __launch_bounds__(64) void screens_kernel(int kind, const double* __r
     const double beta[4] = {beta4.x, beta4.y, beta4.z, beta4.w};
     regularise(m, beta);
     f = stokes(convention);
-    solve(m, &f);
+    solve(m, f);
   } else {  // (S^-1 M^S)^H
 #pragma unroll
     for (int c = 0; c < 4; ++c) {

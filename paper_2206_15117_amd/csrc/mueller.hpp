@@ -1,5 +1,5 @@
-// Image-domain screens Phi_qc(l, m) of the Mueller kernels at one lattice sample, float64, for the host
-// (which refuses singular fields before anything is allocated) and the device (which writes the screens).
+// Image-domain screens Phi_qc(l, m) of the Mueller kernels at one lattice sample, float64, for the device
+// (which writes the screens) and the host's check of the field.
 //
 // Sec. 3.2: Mueller matrices from the Jones matrices of a baseline's two antennas,
 // M = J_a (x) conj(J_b) (identical antennas: J_b = J_a) in correlation order XX, XY, YX, YY (Eq. 3); Stokes form
@@ -15,7 +15,7 @@
 
 #include "polgrid.h"
 
-// Host and device have to agree on which pivots are zero: no product is fused into a sum here.
+// No product is fused into a sum here: host and device see the same matrices.
 #pragma clang fp contract(off)
 
 namespace pg {
@@ -125,9 +125,9 @@ __host__ __device__ inline void regularise(M4& m, const double beta[4]) {
   }
 }
 
-// x <- m^-1 x, m overwritten, by Gauss-Jordan elimination with partial pivoting; false if m is
-// singular.  x may be NULL: only the pivots.  Rows move by selects: registers have no address.
-__host__ __device__ inline bool solve(M4& m, M4* x) {
+// x <- m^-1 x, m overwritten, by Gauss-Jordan elimination with partial pivoting.  Rows move by selects:
+// registers have no address.
+__host__ __device__ inline void solve(M4& m, M4& x) {
 #pragma unroll
   for (int col = 0; col < 4; ++col) {
 #pragma unroll
@@ -135,36 +135,31 @@ __host__ __device__ inline bool solve(M4& m, M4* x) {
       if (size_of(m.a[r][col]) > size_of(m.a[col][col])) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const cd t = m.a[r][j];
+          const cd t = m.a[r][j], v = x.a[r][j];
           m.a[r][j] = m.a[col][j];
+          x.a[r][j] = x.a[col][j];
           m.a[col][j] = t;
-          if (x) {
-            const cd v = x->a[r][j];
-            x->a[r][j] = x->a[col][j];
-            x->a[col][j] = v;
-          }
+          x.a[col][j] = v;
         }
       }
-    if (size_of(m.a[col][col]) == 0.0) return false;
     const cd inv = reciprocal(m.a[col][col]);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (j > col) m.a[col][j] = inv * m.a[col][j];
-      if (x) x->a[col][j] = inv * x->a[col][j];
+      x.a[col][j] = inv * x.a[col][j];
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      if (r == col || (!x && r < col)) continue;
+      if (r == col) continue;
       const cd f = m.a[r][col];
       if (size_of(f) == 0.0) continue;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (j > col) m.a[r][j] = m.a[r][j] - f * m.a[col][j];
-        if (x) x->a[r][j] = x->a[r][j] - f * x->a[col][j];
+        x.a[r][j] = x.a[r][j] - f * x.a[col][j];
       }
     }
   }
-  return true;
 }
 
 }  // namespace pg

@@ -66,3 +66,23 @@ def test_tables_match_the_oracle(mk, os_, support, npol, fields, direction, stor
     slack = floor + 1e-11 * np.abs(want).max()
     assert (np.abs(got.real - want.real) <= unit * np.abs(want.real) + slack).all()
     assert (np.abs(got.imag - want.imag) <= unit * np.abs(want.imag) + slack).all()
+
+
+@pytest.mark.parametrize("ja,jb,eps,refused", [
+    ([1, 1, 1, 1], [1, 1, 1, 1], 0.0, True),      # rank one: a pivot of exactly zero
+    ([1, 1, 1, 1], [1, 1, 1, 1], 0.2, False),     # regularised
+    ([0, 0, 0, 0], [0, 0, 0, 0], 0.0, False),     # a null diagonal is replaced, not refused
+    ([0, 0, 0, 0.1], [-1, 1 + 1j, -1, 0.1], 0.0, False),  # rank one, but rounding leaves no zero
+    ([1e-170, 1, 1, 0.5], [1, 0, 0, 1], 0.2, False),
+    ([np.nan, 0, 0, 1], [1, 0, 0, 1], 0.2, False),
+])
+def test_singular_fields_are_refused_by_their_pivots(ja, jb, eps, refused):
+    pg.use_torch_allocator(True)
+    mk = 4
+    g = synth.Geometry(64, 1e-3, 2, np.zeros(1), np.array([3]), tile=np.array([8]), mk=mk)
+    fields = [np.ascontiguousarray(np.broadcast_to(np.array(j, dtype=complex).reshape(2, 2, 1, 1), (2, 2, mk, mk))) for j in (ja, jb)]
+    if refused:
+        with pytest.raises(pg.PolgridError):
+            pg.make_kernels(g, 4, pg.KIND_GRID, jones=fields[0], jones_b=fields[1], eps_null=eps)
+    else:
+        pg.make_kernels(g, 4, pg.KIND_GRID, jones=fields[0], jones_b=fields[1], eps_null=eps)
