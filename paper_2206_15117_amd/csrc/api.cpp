@@ -87,10 +87,10 @@ int make_kernels_impl(const pg_kernel_spec* spec, hipStream_t s, pg_kernels** ou
 
   const pg_geometry& g = spec->g;
   const int mk = g.mk, np = spec->npol, nqc = np * np;
-  double beta[4];
+  ScreenCheck check;
   std::string err;
   if (generate && !check_screens(np, spec->kind, spec->jones, spec->jones_b, mk, spec->eps_null, spec->stokes_convention,
-                                 beta, err))
+                                 check, err))
     return fail(PG_EINVAL, err);
 
   auto* k = new (std::nothrow) pg_kernels();
@@ -171,7 +171,17 @@ int make_kernels_impl(const pg_kernel_spec* spec, hipStream_t s, pg_kernels** ou
   if (jones) PG_HIP(hipMemcpyAsync(jones, spec->jones, sizeof(double2) * field, hipMemcpyHostToDevice, s), "upload Jones");
   if (jones_b) PG_HIP(hipMemcpyAsync(jones_b, spec->jones_b, sizeof(double2) * field, hipMemcpyHostToDevice, s), "upload Jones");
   PG_HIP(hipMemcpyAsync(aa_d.p, aa.data(), mk * sizeof(double), hipMemcpyHostToDevice, s), "upload AA");
-  PG_HIP(launch_screens(np, spec->kind, jones, jones_b, mk, beta, spec->stokes_convention, phi_d.as<double2>(), s), "screens");
+  PG_HIP(launch_screens(np, spec->kind, jones, jones_b, mk, check.beta, spec->stokes_convention, phi_d.as<double2>(), s), "screens");
+  // Samples that the check solved itself, through the same buffer, as many a time as it holds.
+  const size_t at_a_time = half * sizeof(double2) / (16 * sizeof(double2) + sizeof(uint32_t));
+  for (size_t i = 0; i < check.px.size(); i += at_a_time) {
+    const size_t count = std::min(at_a_time, check.px.size() - i);
+    double2* at = a_d.as<double2>();
+    uint32_t* px = reinterpret_cast<uint32_t*>(at + 16 * count);
+    PG_HIP(hipMemcpyAsync(at, check.phi.data() + 32 * i, 16 * sizeof(double2) * count, hipMemcpyHostToDevice, s), "upload screens");
+    PG_HIP(hipMemcpyAsync(px, check.px.data() + i, sizeof(uint32_t) * count, hipMemcpyHostToDevice, s), "upload screens");
+    PG_HIP(launch_place_screens(px, at, count, npix, phi_d.as<double2>(), s), "screens");
+  }
   GenRound r;
   r.mk = mk;
   r.nqc = nqc;

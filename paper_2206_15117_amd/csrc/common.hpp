@@ -172,6 +172,8 @@ namespace pg {
 // Kernel generation.  jones, jones_b: device copies of the fields or NULL.
 hipError_t launch_screens(int npol, int kind, const double* jones, const double* jones_b, int mk, const double beta[4],
                           int convention, double2* phi, hipStream_t s);
+// phi[cell][px[i]] = at[i][cell] for `count` samples of a 16-cell set; px and at on the device.
+hipError_t launch_place_screens(const uint32_t* px, const double2* at, size_t count, size_t npix, double2* phi, hipStream_t s);
 // Planes whose tables one round of launches makes, and the round's scratch arrays: per plane wterm
 // [mk][mk], twiddles [support os / 2][mk / 2 + 1] and first-stage products [nqc][mk][support os], each with the
 // stride of the set's largest support.
@@ -239,8 +241,14 @@ hipError_t launch_batch_degrid(const pg_batch* b, int flags, hipStream_t s);
 
 // Host numerics (pswf.cpp, mueller.cpp)
 std::vector<double> pswf0(double c, const std::vector<double>& x);
-// Whether the screens of the given kind exist at every lattice sample, and beta of Eq. 6 per diagonal entry.
+// Whether the screens of the given kind exist at every lattice sample, beta of Eq. 6 per diagonal entry, and the
+// screens [q][c] (re, im) of the samples px that the check solves itself.
+struct ScreenCheck {
+  double beta[4];
+  std::vector<uint32_t> px;
+  std::vector<double> phi;  // [px.size()][16][2]
+};
 bool check_screens(int npol, int kind, const double* jones, const double* jones_b, int mk, double eps, int convention,
-                   double beta[4], std::string& err);
+                   ScreenCheck& out, std::string& err);
 
 }  // namespace pg

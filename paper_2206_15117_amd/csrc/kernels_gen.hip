@@ -47,6 +47,13 @@ __global__ __launch_bounds__(64) void screens_kernel(int kind, const double* __r
     for (int c = 0; c < 4; ++c) phi[(q * 4 + c) * npix + px] = make_double2(f.a[q][c].re, f.a[q][c].im);
 }
 
+// The screens of a few samples, solved on the host; 16 threads a sample.
+__global__ void place_screens_kernel(const uint32_t* __restrict__ px, const double2* __restrict__ at, size_t count,
+                                     size_t npix, double2* __restrict__ phi) {
+  const size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
+  if (i < 16 * count) phi[(i % 16) * npix + px[i / 16]] = at[i];
+}
+
 __global__ void unit_screen_kernel(size_t npix, double2* __restrict__ phi) {
   const size_t px = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
   if (px < npix) phi[px] = make_double2(1.0, 0.0);
@@ -341,6 +348,12 @@ hipError_t launch_screens(int npol, int kind, const double* jones, const double*
     hipLaunchKernelGGL(screens_kernel, dim3(static_cast<unsigned>((npix + 63) / 64)), dim3(64), 0, s, kind, jones, jones_b,
                        npix, make_double4(beta[0], beta[1], beta[2], beta[3]), convention, phi);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_place_screens(const uint32_t* px, const double2* at, size_t count, size_t npix, double2* phi, hipStream_t s) {
+  hipLaunchKernelGGL(place_screens_kernel, dim3(static_cast<unsigned>((16 * count + 255) / 256)), dim3(256), 0, s, px, at,
+                     count, npix, phi);
   return hipGetLastError();
 }
 

@@ -1,11 +1,12 @@
 // Host check of the Mueller screens (mueller.hpp): the regularisation of Eq. 6 and the refusal, before anything
 // is allocated, of fields whose regularised matrix has a zero pivot at a lattice sample.  The device
-// writes the screens.
+// writes the screens, except at the samples that come within 1e-6 of singular or far from the normal range.
 //
-// A zero pivot of a singular matrix is a matter of rounding, so which fields are refused is defined by one
-// elimination, `has_zero_pivot`, in library complex arithmetic.  It costs ten times an elimination in plain arithmetic,
-// which therefore goes first and leaves it the samples that come within 1e-6 of singular or far from the
-// normal range: 256^2 samples on 8 cores 28 ms with the library's arithmetic and the screens, 3.3 ms now.
+// A zero pivot of a singular matrix is a matter of rounding, so such a sample has one elimination that both decides
+// and solves, `library::inverse`, in library complex arithmetic: another elimination may meet a zero where this
+// one does not, and its screens would be NaN.  It costs ten times an elimination in plain arithmetic, which
+// therefore goes first and leaves it those samples: 256^2 samples on 8 cores 28 ms with the library's
+// arithmetic everywhere, 3.3 ms where no sample is close.
 #include "mueller.hpp"
 
 #include <algorithm>
@@ -105,32 +106,43 @@ M4 mueller_at(const double* jones, const double* jones_b, size_t npix, size_t px
   return mul(mul(s, m), sinv);
 }
 
-bool has_zero_pivot(M4 w) {
+// Gauss-Jordan with partial pivoting; false at a zero pivot.
+bool inverse(const M4& m, M4& out) {
+  cd w[4][8] = {};
+  for (int i = 0; i < 4; ++i) {
+    for (int j = 0; j < 4; ++j) w[i][j] = m.a[i][j];
+    w[i][i + 4] = 1.0;
+  }
   for (int col = 0; col < 4; ++col) {
     int piv = col;
     for (int r = col + 1; r < 4; ++r)
-      if (std::abs(w.a[r][col]) > std::abs(w.a[piv][col])) piv = r;
-    if (std::abs(w.a[piv][col]) == 0.0) return true;
+      if (std::abs(w[r][col]) > std::abs(w[piv][col])) piv = r;
+    if (std::abs(w[piv][col]) == 0.0) return false;
     if (piv != col)
-      for (int j = 0; j < 4; ++j) std::swap(w.a[piv][j], w.a[col][j]);
-    const cd inv = 1.0 / w.a[col][col];
-    for (int j = 0; j < 4; ++j) w.a[col][j] *= inv;
+      for (int j = 0; j < 8; ++j) std::swap(w[piv][j], w[col][j]);
+    const cd inv = 1.0 / w[col][col];
+    for (int j = 0; j < 8; ++j) w[col][j] *= inv;
     for (int r = 0; r < 4; ++r) {
       if (r == col) continue;
-      const cd f = w.a[r][col];
+      const cd f = w[r][col];
       if (f == 0.0) continue;
-      for (int j = 0; j < 4; ++j) w.a[r][j] -= f * w.a[col][j];
+      for (int j = 0; j < 8; ++j) w[r][j] -= f * w[col][j];
     }
   }
-  return false;
+  for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < 4; ++j) out.a[i][j] = w[i][j + 4];
+  return true;
 }
 }  // namespace library
 
 }  // namespace
 
 bool check_screens(int npol, int kind, const double* jones, const double* jones_b, int mk, double eps, int convention,
-                   double beta[4], std::string& err) {
-  for (int p = 0; p < 4; ++p) beta[p] = 0.0;
+                   ScreenCheck& out, std::string& err) {
+  double(&beta)[4] = out.beta;
+  for (double& b : beta) b = 0.0;
+  out.px.clear();
+  out.phi.clear();
   if (npol == 1 && (jones || jones_b)) {
     err = "npol = 1 (Stokes I only) takes no Jones field";
     return false;
@@ -150,19 +162,24 @@ bool check_screens(int npol, int kind, const double* jones, const double* jones_
     for (int p = 0; p < 4; ++p) beta[p] = std::max(beta[p], mx[p]);
   });
   for (int p = 0; p < 4; ++p) beta[p] *= (eps / 2.0) * (eps / 2.0);
-  std::vector<size_t> close;  // samples for the library's elimination
+  std::vector<uint32_t>& close = out.px;
   parallel_for(samples, [&](size_t px0, size_t px1) {
-    std::vector<size_t> mine;
+    std::vector<uint32_t> mine;
     for (size_t px = px0; px < px1; ++px) {
       M4 m = mueller_at(jones, jones_b, npix, px, u);
       regularise(m, beta);
-      if (!far_from_singular(m)) mine.push_back(px);
+      if (!far_from_singular(m)) mine.push_back(static_cast<uint32_t>(px));
     }
     std::lock_guard<std::mutex> lk(mu);
     close.insert(close.end(), mine.begin(), mine.end());
   });
+  if (samples == 1 && !close.empty()) {
+    close.resize(npix);
+    for (size_t px = 0; px < npix; ++px) close[px] = static_cast<uint32_t>(px);
+  }
   std::atomic<bool> singular{false};
   if (!close.empty()) {
+    out.phi.resize(32 * close.size());
     library::M4 s, sinv;
     library::stokes(convention, s, sinv);
     double top[4] = {0.0, 0.0, 0.0, 0.0};
@@ -184,7 +201,16 @@ bool check_screens(int npol, int kind, const double* jones, const double* jones_
           const double weight = (eps / 2.0) * top[p] * (eps / 2.0) * top[p];
           m.a[p][p] = b * (1.0 + weight / std::norm(b));
         }
-        if (library::has_zero_pivot(m)) singular = true;
+        library::M4 inv;
+        if (!library::inverse(m, inv)) {
+          singular = true;
+          continue;
+        }
+        const library::M4 f = library::mul(inv, s);
+        for (int qc = 0; qc < 16; ++qc) {
+          out.phi[32 * i + 2 * qc] = f.a[qc / 4][qc % 4].real();
+          out.phi[32 * i + 2 * qc + 1] = f.a[qc / 4][qc % 4].imag();
+        }
       }
     });
   }
