@@ -21,7 +21,8 @@
 namespace pg {
 namespace {
 
-// Runs fn(begin, end) over [0, n) split across host threads (per-pixel work is independent).
+// Runs fn(begin, end) over [0, n) split across host threads (per-pixel work is independent).  fn throws nothing and
+// allocates nothing: an exception in a thread ends the process.
 template <class F>
 void parallel_for(size_t n, F fn) {
   const size_t hw = std::max(1u, std::thread::hardware_concurrency());
@@ -162,17 +163,18 @@ bool check_screens(int npol, int kind, const double* jones, const double* jones_
     for (int p = 0; p < 4; ++p) beta[p] = std::max(beta[p], mx[p]);
   });
   for (int p = 0; p < 4; ++p) beta[p] *= (eps / 2.0) * (eps / 2.0);
-  std::vector<uint32_t>& close = out.px;
+  std::vector<uint8_t> near(samples, 0);  // filled in by the threads, which allocate nothing: they have no one to throw to
   parallel_for(samples, [&](size_t px0, size_t px1) {
-    std::vector<uint32_t> mine;
     for (size_t px = px0; px < px1; ++px) {
       M4 m = mueller_at(jones, jones_b, npix, px, u);
       regularise(m, beta);
-      if (!far_from_singular(m)) mine.push_back(static_cast<uint32_t>(px));
+      near[px] = !far_from_singular(m);
     }
-    std::lock_guard<std::mutex> lk(mu);
-    close.insert(close.end(), mine.begin(), mine.end());
   });
+  std::vector<uint32_t>& close = out.px;
+  close.reserve(std::count(near.begin(), near.end(), 1));
+  for (size_t px = 0; px < samples; ++px)
+    if (near[px]) close.push_back(static_cast<uint32_t>(px));
   if (samples == 1 && !close.empty()) {
     close.resize(npix);
     for (size_t px = 0; px < npix; ++px) close[px] = static_cast<uint32_t>(px);

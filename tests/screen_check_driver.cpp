@@ -1,14 +1,31 @@
 // The host's check of Mueller screens against what the device does with its result, on the CPU: every sample of an
 // accepted finite field has finite screens, the check's own where it lists the sample, otherwise those of
-// the elimination that the device runs.
+// the elimination that the device runs.  With the argument `threads`: a field of singular samples large enough to be
+// split over threads, while every allocation outside the main thread fails.
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
+#include <new>
 #include <random>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "common.hpp"
 #include "mueller.hpp"
+
+namespace {
+const std::thread::id g_main = std::this_thread::get_id();
+bool g_main_only = false;
+}  // namespace
+
+void* operator new(std::size_t n) {
+  if (g_main_only && std::this_thread::get_id() != g_main) throw std::bad_alloc();
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
 
 namespace {
 
@@ -52,9 +69,23 @@ void check(const std::vector<double>& ja, const std::vector<double>& jb, int mk,
   }
 }
 
+int threads() {
+  const int mk = 128;
+  std::vector<double> field(8 * mk * mk, 0.0);
+  for (size_t i = 0; i < field.size(); i += 2) field[i] = i < 4u * mk * mk ? 0.3 : 0.7;
+  pg::ScreenCheck out;
+  std::string err;
+  g_main_only = true;
+  const bool refused = !pg::check_screens(4, PG_KIND_GRID, field.data(), nullptr, mk, 0.0, PG_STOKES_IAU, out, err);
+  g_main_only = false;
+  std::printf("%s, %zu samples near\n", refused ? "refused" : "accepted", out.px.size());
+  return out.px.size() == static_cast<size_t>(mk) * mk ? 0 : 1;
+}
+
 }  // namespace
 
-int main() {
+int main(int argc, char** argv) {
+  if (argc > 1 && std::string(argv[1]) == "threads") return threads();
   std::mt19937_64 rng(7);
   std::uniform_real_distribution<double> u(-1.0, 1.0);
   Tally t;

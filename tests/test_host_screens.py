@@ -27,3 +27,9 @@ def driver(tmp_path_factory):
 def test_accepted_fields_have_finite_screens(driver):
     res = subprocess.run([driver], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_the_threads_allocate_nothing(driver):
+    """Memory that runs out inside a worker thread would end the process: allocations there throw in this run."""
+    res = subprocess.run([driver, "threads"], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
