@@ -18,6 +18,7 @@
 // (more records to reduce), 96- and 128-pixel tiles 16 us (too few workgroups in the patch).
 // The subtraction is written without contraction (product rounded, then difference rounded) so that
 // the float32 reference reproduces it bit for bit.
+#include "clean_state.hpp"
 #include "common.hpp"
 
 #include <mutex>
@@ -26,20 +27,13 @@
 namespace pg {
 namespace {
 
-struct CleanState {
-  int done;
-  int ncomp;
-};
-
 __device__ inline unsigned long long peak_key(float a, int64_t idx) {
   return (static_cast<unsigned long long>(__float_as_uint(a)) << 32) |
          static_cast<unsigned long long>(0xFFFFFFFFu - static_cast<uint32_t>(idx));
 }
 
 __global__ __launch_bounds__(256) void peak_kernel(const float* __restrict__ stokes_i, const uint8_t* __restrict__ mask,
-                                                   int64_t npix, unsigned long long* __restrict__ slot,
-                                                   const CleanState* __restrict__ st) {
-  if (st->done) return;
+                                                   int64_t npix, unsigned long long* __restrict__ slot) {
   unsigned long long best = 0;
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < npix;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -170,10 +164,7 @@ __global__ __launch_bounds__(kCleanThreads) void clean_start_kernel(float* __res
                                                                     CleanState* __restrict__ st,
                                                                     TileBest* __restrict__ out) {
   __shared__ unsigned long long wbest[kCleanThreads / 64];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->done = 0;
-    st->ncomp = 0;
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->stop = kCleanRuns;
   const float none[NPOL] = {};
   clean_tile<NPOL>(residual, residual, mask, g, 0, 0, 0, 0, 0, 0, none, out, wbest);
 }
@@ -191,7 +182,7 @@ __global__ __launch_bounds__(kCleanThreads) void clean_step_kernel(float* __rest
                                                                    float* __restrict__ model) {
   __shared__ unsigned long long wbest[kCleanThreads / 64];
   __shared__ float shared_value[NPOL];
-  // thread t fetches tile t's whole record and the done flag at once: each is a trip past the L2
+  // thread t fetches tile t's whole record and the cycle's state at once: each is a trip past the L2
   // (another XCD wrote them), and the trips of an iteration are most of its time
   const int tiles = g.across * g.across;
   TileBest mine;
@@ -203,14 +194,11 @@ __global__ __launch_bounds__(kCleanThreads) void clean_step_kernel(float* __rest
     const TileBest other = in[t];
     if (other.key > mine.key) mine = other;
   }
-  if (st->done) return;
+  if (clean_over(st->stop, step)) return;
   const unsigned long long key = workgroup_best(mine.key, wbest);
   const float a = __uint_as_float(static_cast<uint32_t>(key >> 32));
   if (key == 0 || !(a >= threshold)) {  // the same verdict in every workgroup
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      st->done = 1;
-      st->ncomp = step;
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->stop = step;
     return;
   }
   if (mine.key == key) {
@@ -243,14 +231,10 @@ __global__ __launch_bounds__(kCleanThreads) void clean_step_kernel(float* __rest
   clean_tile<NPOL>(residual, psf, mask, g, py, px, y0, y1, x0, x1, value, out, wbest);
 }
 
-__global__ void clean_init_kernel(CleanState* st, unsigned long long* slot) {
-  st->done = 0;
-  st->ncomp = 0;
-  *slot = 0;
-}
+__global__ void peak_init_kernel(unsigned long long* slot) { *slot = 0; }
 
 __global__ void clean_count_kernel(const CleanState* st, int max_iter, int32_t* n_comp) {
-  *n_comp = st->done ? st->ncomp : max_iter;
+  *n_comp = clean_components(st->stop, max_iter);
 }
 
 // img[i] / ref for every pixel, ref = img[ref_index] read first into `held` (one thread), so the
@@ -295,11 +279,10 @@ hipError_t hogbom_static_scratch(void** out, size_t* bytes) {
 }
 
 hipError_t launch_masked_peak(const float* img, const uint8_t* mask, int64_t npix, void* scratch, hipStream_t s) {
-  auto* st = static_cast<CleanState*>(scratch);
   auto* slot = reinterpret_cast<unsigned long long*>(static_cast<char*>(scratch) + 256);
-  hipLaunchKernelGGL(clean_init_kernel, dim3(1), dim3(1), 0, s, st, slot);
+  hipLaunchKernelGGL(peak_init_kernel, dim3(1), dim3(1), 0, s, slot);
   const int blocks = static_cast<int>(std::min<int64_t>((npix + 255) / 256, 1024));
-  hipLaunchKernelGGL(peak_kernel, dim3(blocks), dim3(256), 0, s, img, mask, npix, slot, st);
+  hipLaunchKernelGGL(peak_kernel, dim3(blocks), dim3(256), 0, s, img, mask, npix, slot);
   return hipGetLastError();
 }
 
