@@ -590,9 +590,12 @@ struct GridRun {
     lds_add(at + im_off, fixed_bits(yi));
   }
 
-  // PAIRS row pairs from pair P0 on; at = the tap's byte offset in the footprint
+  // PAIRS row pairs from pair P0 on; at = the tap's byte offset in the footprint, on = whether this lane has a tap.
+  // The products run with every lane on: they read their coefficients from lanes 0 to 15 whatever the mask, so those
+  // lanes' registers must hold them there, with or without a tap.  (They are convergent operations, which
+  // the compiler keeps out of the masked additions.)
   template <int P0, int PAIRS>
-  __device__ __forceinline__ void pairs(uint32_t at, const float2 (&tap)[NQ * NP]) const {
+  __device__ __forceinline__ void pairs(uint32_t at, const float2 (&tap)[NQ * NP], bool on) const {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       MfmaF4 y0 = {0.0f, 0.0f, 0.0f, 0.0f}, y1 = y0;
@@ -604,11 +607,13 @@ struct GridRun {
         y0 = __builtin_amdgcn_mfma_f32_4x4x1f32(a_re[c], t.x, y0, 4, P0, 0);
         if constexpr (PAIRS > 1) y1 = __builtin_amdgcn_mfma_f32_4x4x1f32(a_re[c], t.x, y1, 4, P0 + 1, 0);
       }
-      add(at + d[2 * P0], y0[0], y0[1]);
-      add(at + d[2 * P0 + 1], y0[2], y0[3]);
-      if constexpr (PAIRS > 1) {
-        add(at + d[2 * P0 + 2], y1[0], y1[1]);
-        add(at + d[2 * P0 + 3], y1[2], y1[3]);
+      if (on) {
+        add(at + d[2 * P0], y0[0], y0[1]);
+        add(at + d[2 * P0 + 1], y0[2], y0[3]);
+        if constexpr (PAIRS > 1) {
+          add(at + d[2 * P0 + 2], y1[0], y1[1]);
+          add(at + d[2 * P0 + 3], y1[2], y1[3]);
+        }
       }
       at += plane_bytes;
     }
@@ -629,17 +634,17 @@ struct GridRun {
     }
   }
 
-  __device__ __forceinline__ void apply(int count, uint32_t at, const float2 (&tap)[NQ * NP]) const {
+  __device__ __forceinline__ void apply(int count, uint32_t at, const float2 (&tap)[NQ * NP], bool on) const {
     if (count >= 4) {
-      pairs<0, 2>(at, tap);
+      pairs<0, 2>(at, tap, on);
       if (count == 8)
-        pairs<2, 2>(at, tap);
+        pairs<2, 2>(at, tap, on);
       else if (count >= 6)
-        pairs<2, 1>(at, tap);
+        pairs<2, 1>(at, tap, on);
     } else if (count >= 2) {
-      pairs<0, 1>(at, tap);
+      pairs<0, 1>(at, tap, on);
     }
-    if (count & 1) odd(at, tap);
+    if ((count & 1) && on) odd(at, tap);
   }
 };
 
@@ -773,7 +778,7 @@ __device__ __forceinline__ void grid_item_shared(const Item it, const int2* __re
         gr.set(j, run, m_off, mv, lane);
         cur = start;
       }
-      if (pass < full || tail_lane) gr.apply(run, lds_base + static_cast<uint32_t>(cur.off) * 8u, tap);
+      gr.apply(run, lds_base + static_cast<uint32_t>(cur.off) * 8u, tap, pass < full || tail_lane);
       if (step.dt == 0)
         cur.off += step.doff;
       else
