@@ -16,6 +16,7 @@
 #include <cmath>
 
 #include "mosaic.hpp"
+#include "weight_normalise.hpp"
 
 namespace pg {
 namespace {
@@ -146,20 +147,14 @@ __global__ __launch_bounds__(256) void reproject_kernel(const float* __restrict_
 template <typename V>
 __global__ __launch_bounds__(256) void weight_normalise_kernel(V* __restrict__ img, const V* __restrict__ weight,
                                                                int64_t count, int npol, float min_weight) {
-  constexpr int n = sizeof(V) / 4;
   for (int64_t p = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; p < count;
        p += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    float w[n];
-    *reinterpret_cast<V*>(w) = weight[p];
-    bool any = false;
-#pragma unroll
-    for (int e = 0; e < n; ++e) any = any || w[e] >= min_weight;
+    const Pixels<V> w(weight[p]);
+    const bool any = any_reaches(w, min_weight);
     for (int q = 0; q < npol; ++q) {
-      float v[n] = {};
-      if (any) *reinterpret_cast<V*>(v) = img[q * count + p];
-#pragma unroll
-      for (int e = 0; e < n; ++e) v[e] = w[e] >= min_weight ? v[e] / w[e] : 0.0f;
-      img[q * count + p] = *reinterpret_cast<const V*>(v);
+      Pixels<V> v;
+      if (any) v = Pixels<V>(img[q * count + p]);
+      img[q * count + p] = over_weight(v, w, min_weight);
     }
   }
 }
