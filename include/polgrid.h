@@ -203,7 +203,9 @@ void pg_plan_destroy(pg_plan* p);
  * 2 = row-band ownership, 3 = shared taps with fixed-point LDS accumulation (PG_VARIANT_SHARED);
  * grid_waves and degrid_waves = waves per workgroup, 4, 6, 8 or 16;
  * xcd_group = how many consecutive work items (in plan order) run on one XCD, so that they share
- * its L2 (1 = plain order, up to 4096); grid_planes = output correlation planes per row-band
+ * its L2 (1 = plain order, up to 4096; shared taps with grid_planes 1 or 2 take it as the most and
+ * halve it while the parts of an average plane's kernels that as many workgroups of one item read
+ * exceed the XCD's 4 MB of L2); grid_planes = output correlation planes per row-band
  * workgroup, 0 (all), 1, 2 or 4: with 1 or 2, npol / grid_planes workgroups share each work item,
  * each holding only its planes' sub-grid in LDS and reading only its rows of the 4x4 Mueller
  * kernels (ignored where it does not divide npol); degrid_corrs = output correlations per degrid

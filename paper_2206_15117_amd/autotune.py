@@ -155,6 +155,13 @@ def _time(fn, reps):
     return e0.elapsed_time(e1) / reps
 
 
+def best_group(ms):
+    """The smallest XCD group within 1 % of the fastest (two runs of one launch differ by less).  The shared-tap gridder
+    caps the group to what the L2 holds of its tables, so several groups can be the same launch: the least of them."""
+    limit = 1.01 * min(ms.values())
+    return min(g for g, t in ms.items() if t <= limit)
+
+
 def tune(geom, npol, jones, uvw, vis, eps_null=0.2, storage=0, reps=3, wgs=(1, 2, 3, 4),
          waves=(4, 6, 8, 16), chunks=(256, 1024), planes=(0, 2, 1), verbose=True):
     """Time every candidate; returns (best dict, list of all results)."""
@@ -208,16 +215,16 @@ def tune(geom, npol, jones, uvw, vis, eps_null=0.2, storage=0, reps=3, wgs=(1, 2
     kg = pg.make_kernels(g, npol, pg.KIND_GRID, jones=jones, eps_null=eps_null, storage=storage)
     kd = pg.make_kernels(g, npol, pg.KIND_DEGRID, jones=jones, storage=storage)
     p = pg.plan(kg, uvw, max_chunk=bg["max_chunk"])
-    best_x = (float("inf"), 1)
+    group_ms = {}
     for xg in (1, 2, 4, 8, 16, 32):
         p.set_launch(bg["variant"], bg["waves"], bd["waves"], xg, bg["planes"], bd["corrs"])
         t = (_time(lambda: pg.grid(p, kg, vis, out=grid, fftshift=True), reps)
              + _time(lambda: pg.degrid(p, kd, grid, out=out, fftshift=True), reps))
+        group_ms[xg] = t
         results.append(dict(xcd_group=xg, grid_plus_degrid_ms=t))
         if verbose:
             print(json.dumps(results[-1]), flush=True)
-        best_x = min(best_x, (t, xg))
-    best["xcd_group"] = best_x[1]
+    best["xcd_group"] = best_group(group_ms)
     return best, results
 
 
