@@ -76,13 +76,13 @@ extern "C" {
                                without either flag the library picks by sub-grid width.
                                Both give the same result up to float32 summation order. */
 #define PG_VARIANT_SHARED 32 /* pg_grid: force the shared-tap kernel: rows of one kernel phase share
-                                each tap load, and the sub-grid is summed exactly in two-word fixed
+                                each tap load, and the sub-grid is summed exactly in 51-bit fixed
                                 point with LDS integer atomics (per item and plane, scaled from a
                                 bound on its values); an item with a non-finite visibility turns
                                 its grid points into NaN.  Needs twice one output plane's sub-grid
                                 in LDS; where that does not fit the row-band kernel runs instead */
 #define PG_DETERMINISTIC 16 /* pg_grid: bit-for-bit reproducible result.  Each work item's sub-grid
-                               is summed exactly (the shared-tap kernel's fixed point, 8 waves and
+                               is summed exactly (the shared-tap kernel's fixed point, 16 waves and
                                one output plane per workgroup whatever the plan's launch settings;
                                where that does not fit the LDS, row bands in a fixed order), and
                                the sub-grids are added
@@ -333,7 +333,7 @@ int pg_scale_rows(float* x, int64_t rows, int64_t cols, const float* scale, void
  *             fraction eps of its peak, Sec. 3.3) or NULL for every pixel;
  *   comp_pos  int32 [max_iter] flat pixel indices, comp_val float32 [max_iter][npol];
  *   n_comp    int32 [1] (device): the number of components found.
- * All pointers are device memory.  Enqueue only (3 launches per iteration of the budget; the
+ * All pointers are device memory.  Enqueue only (one launch per iteration of the budget; the
  * launches after the stop return at once).  Errors: PG_EINVAL, PG_ENOMEM, PG_EHIP. */
 int pg_hogbom(float* residual, const float* psf, const uint8_t* mask, int32_t n, int32_t npol, float gain,
               float threshold, int32_t psf_patch, int32_t max_iter, int32_t* comp_pos, float* comp_val, float* model,
@@ -354,10 +354,11 @@ int pg_normalise_at(float* img, int64_t count, int64_t ref_index, void* stream);
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and
  * kernels as pg_hogbom; the scratch pg_hogbom allocates per call (iteration state and two sets of
  * tile records) is instead a fixed device array of the library, about 64 KiB on each GPU it runs on,
- * held until the process ends.  Every call on one GPU shares that GPU's array, so calls that overlap on one GPU (other
- * streams or threads) race; each call writes the part it uses before its first iteration.  Only
- * kernel launches are enqueued (no hipMalloc, hipFree, memset or copy).  Errors: as pg_hogbom, and
- * PG_EINVAL when max_iter exceeds PG_HOGBOM_STATIC_MAX_ITER. */
+ * held until the process ends.  Every call on one GPU shares that GPU's array, so calls that overlap
+ * on one GPU (other streams or threads) race; each call writes the part it uses before its first
+ * iteration.  Only kernel launches are enqueued (no hipMalloc, hipFree, memset or copy).  Errors: as
+ * pg_hogbom, and PG_EINVAL when max_iter exceeds PG_HOGBOM_STATIC_MAX_ITER (a limit of this entry
+ * point; the array does not depend on it). */
 #define PG_HOGBOM_STATIC_MAX_ITER 65536
 int pg_hogbom_noalloc(float* residual, const float* psf, const uint8_t* mask, int32_t n, int32_t npol, float gain,
                       float threshold, int32_t psf_patch, int32_t max_iter, int32_t* comp_pos, float* comp_val,

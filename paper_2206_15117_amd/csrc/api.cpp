@@ -739,9 +739,7 @@ int pg_hogbom_noalloc(float* residual, const float* psf, const uint8_t* mask, in
                                std::to_string(PG_HOGBOM_STATIC_MAX_ITER) + ") for pg_hogbom_noalloc");
   const int patch = (psf_patch <= 0 || psf_patch > n) ? n : psf_patch;
   void* scratch = nullptr;
-  size_t bytes = 0;
-  PG_HIP(hogbom_static_scratch(&scratch, &bytes), "hogbom_noalloc scratch address");
-  if (hogbom_scratch_bytes() > bytes) return fail(PG_EINVAL, "scratch too small");
+  PG_HIP(hogbom_static_scratch(&scratch), "hogbom_noalloc scratch address");
   PG_HIP(launch_hogbom(residual, psf, mask, n, npol, gain, threshold, patch, max_iter, comp_pos, comp_val, model,
                        n_comp, scratch, static_cast<hipStream_t>(stream)),
          "hogbom_noalloc");

@@ -253,15 +253,14 @@ __global__ void divide_by_held_kernel(float* __restrict__ img, int64_t count, co
 // Scratch of the allocation-free entry point: the iteration state and two sets of tile records.  Each
 // GPU holds its own copy; host code reaches it only through the address hipGetSymbolAddress returns on
 // that device.
-constexpr size_t kStaticScratchBytes = kCleanScratchBytes;
-__device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+__device__ __align__(256) unsigned char scratch[kCleanScratchBytes];
 
 std::mutex g_static_mu;
 std::vector<void*> g_static_ptr;  // per device, looked up once with that device current
 
 }  // namespace
 
-hipError_t hogbom_static_scratch(void** out, size_t* bytes) {
+hipError_t hogbom_static_scratch(void** out) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
@@ -274,7 +273,6 @@ hipError_t hogbom_static_scratch(void** out, size_t* bytes) {
     g_static_ptr[dev] = ptr;
   }
   *out = g_static_ptr[dev];
-  *bytes = kStaticScratchBytes;
   return hipSuccess;
 }
 

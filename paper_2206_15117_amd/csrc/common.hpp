@@ -168,8 +168,7 @@ struct pg_batch {
 // ---- launchers implemented in the .hip files (all enqueue on `s`)
 namespace pg {
 
-// Kernel generation (kernels_gen.hip)
-// Kernel generation.  jones, jones_b: device copies of the fields or NULL.
+// Kernel generation (kernels_gen.hip).  jones, jones_b: device copies of the fields or NULL.
 hipError_t launch_screens(int npol, int kind, const double* jones, const double* jones_b, int mk, const double beta[4],
                           int convention, double2* phi, hipStream_t s);
 // phi[cell][px[i]] = at[i][cell] for `count` samples of a 16-cell set; px and at on the device.
@@ -235,7 +234,7 @@ hipError_t launch_hogbom(float* residual, const float* psf, const uint8_t* mask,
 hipError_t launch_masked_peak(const float* img, const uint8_t* mask, int64_t npix, void* scratch, hipStream_t s);
 hipError_t launch_normalise_at(float* img, int64_t count, int64_t ref_index, float* held, hipStream_t s);
 // Device address (on the current device) and size of the fixed scratch array of pg_hogbom_noalloc.
-hipError_t hogbom_static_scratch(void** out, size_t* bytes);
+hipError_t hogbom_static_scratch(void** out);
 hipError_t launch_batch_grid(const pg_batch* b, int flags, hipStream_t s);
 hipError_t launch_batch_degrid(const pg_batch* b, int flags, hipStream_t s);
 

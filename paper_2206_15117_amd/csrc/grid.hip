@@ -545,7 +545,9 @@ constexpr int shared_waves_per_simd(int nw, int nq) { return nw == 16 && nq == 1
 // ALU.  The order of the products and their rounding are those of a chain of float FMAs either way.
 // What limits this loop is how often a wave can issue (5 to 8 cycles from one of its instructions to
 // the next, whatever the unit), so it wants few instructions and many waves: the rows' offsets and
-// the odd row's values stay scalar, and the state fits 64 vector registers (8 waves per SIMD).
+// the odd row's values stay scalar, and 64 vector registers (8 waves per SIMD) have to do.  With float32 tables, four
+// correlations and one plane they are four or five too few: the start of the tap walk is among the
+// spilled, and its reload at a run's first step waits for the taps requested just before.
 constexpr int kGridRun = 8;
 typedef __attribute__((address_space(3))) unsigned long long LdsWord;
 
@@ -1083,8 +1085,9 @@ __device__ __forceinline__ void degrid_sum_rows(float (&acc)[R][2 * NC], int j, 
 // Bound: vector instruction issue (the loop is 92 to 95 % FMAs, 64 a row and 64 taps), at the four waves a
 // SIMD that four planes of sub-grid in LDS leave.  Runs in a wave are three to five rows long at 300 rows an item, so every length
 // up to the longest has its own pass: a run of 7 taken as 4 + 2 + 1 loaded its taps three times.  2.3 M rows,
-// 2048^2: 2.31 ms, 2.49 with passes of 8, 4, 2 and 1.  (The same sums on v_mfma_f32_4x4x1 took 2.9 ms: pairs of rows
-// and 16 taps an instruction leave too few products to hide a step's loads behind.)
+// 2048^2, a call of pg_degrid: 2.42 ms, 2.61 with passes of 8, 4, 2 and 1.  (The same sums on v_mfma_f32_4x4x1 took 2.96 ms
+// against 2.58 with those passes on the same box: pairs of rows and 16 taps an instruction leave too few products to
+// hide a step's loads behind.)
 constexpr int kDegridRun = 8;  // longest run of same-phase rows whose tap loads one degrid pass shares
 
 template <int NP, typename TapT, int R, int NC = NP>
@@ -1330,11 +1333,13 @@ hipError_t run_grid_banded(const pg_plan* p, const pg_kernels* k, const float2* 
 }
 
 // Workgroups of one item that an XCD takes in a row when each computes NQ of its planes from its own rows
-// of the Mueller tables: as many as the plan's group asks for, but no more than keep a plane's table in the XCD's 4 MB of
-// L2, half of them until it fits.  A set of larger supports reads its tables from beyond L2 otherwise: 6 M rows on 4096^2
-// with one plane a workgroup and 3.3 MB a plane and part, 26.5 ms in groups of four, 21.0 of two, 18.1 of one.
-// Where two parts fit, sharing an item's visibilities is worth more: 0.70 M rows on 1500^2 at 1.1 MB, 0.80 ms, 0.83
-// and 0.90; 2.3 M rows on 2048^2 at 1.9 MB, 2.68, 2.56 and 2.58.
+// of the Mueller tables: as many as the plan's group asks for, but no more than keep their parts of an average plane's table
+// in the XCD's 4 MB of L2, half of them until they fit.  A set of larger supports reads its tables from beyond L2
+// otherwise: 6 M rows on 4096^2 with one plane a workgroup and 3.3 MB a plane and part, 26.5 ms in groups of four, 21.0 of
+// two, 18.1 of one.  Where two parts fit, sharing an item's visibilities is worth more: 0.70 M rows on 1500^2 at
+// 1.1 MB, 0.80 ms, 0.83 and 0.90; 2.3 M rows on 2048^2 at 1.9 MB, 2.68, 2.56 and 2.58.  The average decides, not the
+// largest plane: in the 2.3 M-row set a part of 48 taps a side (4.7 MB) does not fit by itself, but planes from 40
+// taps on carry 2 % of its row-taps, and a line drawn by them would end the sharing in the others.
 template <int NP, int NQ>
 int shared_group(const pg_plan* p, const pg_kernels* k) {
   const size_t part = k->table.bytes / k->nplanes / (NP / NQ);
@@ -1347,7 +1352,7 @@ template <int NP, typename TapT, int NW, int NQ = NP>
 hipError_t run_grid_shared(const pg_plan* p, const pg_kernels* k, const float2* vis, float2* grid, int flags,
                            hipStream_t s) {
   auto fn = grid_shared_kernel<NP, TapT, NW, NQ>;
-  const size_t sub = 2 * (k->lds_bytes / NP * NQ);  // coarse and fine words
+  const size_t sub = 2 * (k->lds_bytes / NP * NQ);  // real and imaginary words
   const size_t bytes = sub + kSharedScratch;
   hipError_t e = allow_lds(fn, bytes);
   if (e != hipSuccess) return e;

@@ -51,8 +51,10 @@ struct FrameD {
   double cell, inv_cell;  // inv_cell: 1 / cell, rounded; 0 where that or the quotient's remainder may leave the normal range
 };
 
-// x / cell from the rounded reciprocal: one Newton step on the quotient rounds it correctly (Markstein
-// 1990), in three instructions; a division by an unknown takes a dozen.
+// x / cell from the rounded reciprocal and one Newton step on the quotient (Markstein 1990), in three
+// instructions; a division by an unknown takes a dozen.  The starting quotient may be further off than the
+// theorem's unit in the last place, so the rounding is not proven correct; the division gave the same value for
+// 2e8 random x in (-1, 1) and cells of 1e-6 to 1e-2, and a last place is 1e-16 of a pixel.
 __device__ inline double over_cell(double x, FrameD f) {
   if (f.inv_cell == 0.0) return x / f.cell;
   const double q = x * f.inv_cell;

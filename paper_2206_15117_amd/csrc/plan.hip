@@ -521,7 +521,7 @@ hipError_t launch_plan_sort(const PlanSort& a, int32_t* perm, const int32_t** co
 hipError_t launch_plan_items(const PlanSort& a, int64_t n_kept, int64_t n_items, const int32_t* perm, int2* fine,
                              Item* items, hipStream_t s) {
   if (n_kept == 0) return hipSuccess;
-    return a.bits <= 32 ? run_items<uint32_t>(a, n_kept, n_items, perm, fine, items, s)
+  return a.bits <= 32 ? run_items<uint32_t>(a, n_kept, n_items, perm, fine, items, s)
                       : run_items<uint64_t>(a, n_kept, n_items, perm, fine, items, s);
 }
 
