@@ -602,11 +602,19 @@ def bench_mosaic(steps, warmup):
     torch.cuda.synchronize()
     wall = (time.perf_counter() - t0) / steps
     ms = {k: float(sum(a.elapsed_time(b) for a, b in v) / steps) for k, v in ev.items()}
-    # reprojection roofline: algorithmic HBM bytes per destination pixel (each source value read
-    # once, destination and weight read-modified-written): to the mosaic 4 x (4 + 8) + 4 + 8 B,
-    # to a field 4 x (4 + 4) B
-    b_mos = nf * mframe.n ** 2 * (4 * 12 + 12)
-    b_fld = nf * n * n * 4 * 8
+    # reprojection roofline: the HBM bytes of the pixels that are touched.  To the mosaic, four planes and a weight
+    # are read (20 B) where a field covers a mosaic pixel and 8 (4 + 1) = 40 B read and written where its weight
+    # there is not zero; to a field, 16 B are read where the mosaic covers it and 16 B written everywhere.
+    b_mos = b_fld = 0
+    seen, wseen = torch.empty_like(mw), torch.empty((n, n), dtype=torch.float32, device=mw.device)
+    plane, fplane = torch.empty_like(mimg[:1]), torch.empty_like(img[:1])
+    for f in range(nf):
+        pg.reproject(img[:1], frames[f], plane, mframe, dst_weight=seen)
+        b_mos += 20 * int((seen != 0).sum())
+        pg.reproject(img[:1], frames[f], plane, mframe, src_weight=wimg, dst_weight=seen)
+        b_mos += 40 * int((seen != 0).sum())
+        pg.reproject(mimg[:1], mframe, fplane, frames[f], dst_weight=wseen)
+        b_fld += 16 * int((wseen != 0).sum()) + 16 * n * n
     rep_gbs = (b_mos + b_fld) / ((ms["reproject_to_mosaic"] + ms["reproject_to_field"]) * 1e-3) / 1e9
     return {"workload": f"7-field image-domain mosaic of the major cycle: {nf} fields x {n}x{n}x4 (own phase centres, "
                         f"hexagon at 0.5 deg; rows stored about the mosaic centre and phase-rotated per field), "
